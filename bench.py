@@ -192,29 +192,43 @@ def counters_traffic(workload: str, mode: str = "detect"):
         return None
 
 
+FFT_BLOCK_POINTS = 4096    # transforms of sample blocks: points, twice the samples of a block
+
+
+def block_spectra_bytes(n: int, tmax: int) -> float:
+    """HBM bytes of one sequence's spectra in the FFT scores by sample blocks: those
+    of its blocks written and read, those of its lag tiles written and read."""
+    half = FFT_BLOCK_POINTS // 2
+    return 2.0 * 16 * half * (-(-n // half) + -(-tmax // half))
+
+
 def fft_stage_bytes(wl, plan) -> float:
     """HBM bytes the FFT score stage moves per call, for the transform lengths of
-    the plan (`describe_plan`): the samples read once by the column transforms
+    the plan (`describe_plan`): the samples read once by the forward transforms
     (the centring sums come with the window statistics), the first and last
-    Tmax samples of each sequence read and their head and tail sums written
-    and read back, each pair's complex fp64 transform written by the column
-    kernel, read and written by the row kernel and read by the inverse column
-    kernel (none of that up to 2048 points, where a pair stays in LDS), and the
-    per-channel D(T) written.  With the wrap correction: the first and last M
-    samples read again, the head and tail transforms written, read, the cross
-    spectrum written and read back (six sweeps of the head-tail length), and
-    the M wrap terms per sequence written and read."""
+    Tmax samples of each sequence read and the energies of each lag written
+    and read back, the per-channel D(T) written, and the spectra.  By sample
+    blocks (transforms shorter than N + Tmax, and no wrap term): those of the
+    blocks and of the lag tiles.  Otherwise each pair's complex fp64 transform
+    written by the column kernel, read and written by the row kernel and read by
+    the inverse column kernel (none of that up to 2048 points, where a pair stays
+    in LDS), and with the wrap correction the first and last M samples read
+    again, the head and tail transforms written, read, the cross spectrum
+    written and read back (six sweeps of the head-tail length), and the M wrap
+    terms per sequence written and read."""
     s = wl.num_windows * wl.num_channels
     pairs = (s + 1) // 2
     length = plan["fft_len"]
     lags = wl.tmax - wl.tmin + 1
-    sweeps = 0 if length <= 2048 else 4
-    edges = 2 * 4 * s * wl.tmax + 2 * 8 * s * (wl.tmax + 1) + 2 * 8 * s * lags
-    total = 4 * s * wl.n + edges + sweeps * 16 * pairs * length + 8 * s * lags
+    edges = 2 * 4 * s * wl.tmax + 8 * s * (wl.tmax + 1) + 8 * s * lags
+    total = 4 * s * wl.n + edges + 8 * s * lags
     m = plan["fft_wrap_lags"]
     if plan["fft_wrap_len"]:
         total += 2 * 4 * s * m + 6 * 16 * pairs * plan["fft_wrap_len"] + 2 * 8 * s * m
-    return float(total)
+    elif length < wl.n + wl.tmax:
+        return float(total + s * block_spectra_bytes(wl.n, wl.tmax))
+    sweeps = 0 if length <= 2048 else 4
+    return float(total + sweeps * 16 * pairs * length)
 
 
 def pow2_at_least(v: int, lo: int = 64) -> int:
@@ -222,17 +236,6 @@ def pow2_at_least(v: int, lo: int = 64) -> int:
     while length < v:
         length *= 2
     return length
-
-
-def transform_bytes(pairs_lengths, seq_samples: int, seqs: int, lag_counts) -> float:
-    """HBM bytes of the FFT scores of a batch: every pair of sequences (length L
-    of its transform) writes, reads, writes and reads its complex fp64 transform
-    (none of that up to 2048 points, where a pair stays in LDS); the samples
-    are read once, the head and tail sums written and read back, and D(T)
-    written per lag."""
-    sweeps = sum(16 * 4 * length for length in pairs_lengths if length > 2048)
-    edges = sum(2 * 4 * t + 2 * 8 * (t + 1) + 2 * 8 * t for t in lag_counts)
-    return float(4 * seq_samples + edges + sweeps + 8 * sum(lag_counts))
 
 
 def call_roofline(kernel, bound, work, ms, extra=None):
@@ -806,24 +809,11 @@ def bench_rolling(args):
     pairs_c = sum(c * lag_sum(n, tm) for n, tm in suffix if tm >= wl.tmin)
     if args.fft_scores:
         work = fft_stage_bytes(wl, pkg.describe_plan(desc))   # the whole-window pass
-        # suffix pass: slots j of window b are sequences (b * jmax + j) * C + c,
-        # paired two by two; a pair's transform holds its longer suffix
-        jmax = int(np.floor((2 + params.c_eval * params.step - params.c_measure) / params.step)) + 2
-        need = np.zeros(wl.num_windows * jmax * c, dtype=np.int64)
-        tms = []
-        for b in range(wl.num_windows):
-            for j, st in enumerate(res["starts"][b][:res["n_windows"][b]]):
-                n_j = wl.n - int(st)
-                tm = min(wl.tmax, n_j // 2)
-                for ch in range(c):
-                    need[(b * jmax + j) * c + ch] = n_j + tm
-                    tms.append(tm)
-        if need.size % 2:
-            need = np.append(need, 0)
-        lens = [pow2_at_least(int(v)) for v in need.reshape(-1, 2).max(axis=1) if v > 0]
-        work += transform_bytes(lens, sum(n * c for n, _ in suffix), len(tms), tms)
-        roofline = call_roofline("both FFT score passes (whole windows, then suffix windows "
-                                 "by length class)", "hbm", work, ev_ms,
+        # suffix pass: every suffix by sample blocks of its own
+        for n_j, tm in suffix:
+            work += c * (4 * n_j + 2 * 4 * tm + 3 * 8 * tm + block_spectra_bytes(n_j, tm))
+        roofline = call_roofline("both FFT score passes (whole windows, then suffix windows, "
+                                 "by sample blocks)", "hbm", work, ev_ms,
                                  {"bytes_per_launch": work})
     elif args.mfma_scores:
         work = MFMA_OPS_PER_PAIR * (pairs_a + pairs_c)

@@ -45,9 +45,14 @@
  * of its circular autocorrelation then carry the products of the first and
  * the last M = Tmax - (L - N) samples, which a second transform of at least
  * 2M points computes and which are subtracted (gpoeo_pd_describe_plan reports
- * both lengths).  A rigorous absolute error bound of each D_c(T), from the
- * channel norms, decides which scores are within 1e-6 relative of the exact
- * value; every other lag (exact zeros included) is recomputed as an fp64 sum
+ * both lengths).  A batch of more than eight sequences with lags up to 2^17
+ * takes r from 4096-point transforms of blocks of 2048 samples instead: the
+ * products of two blocks' spectra, summed over all pairs of blocks a given
+ * number of blocks apart, give r at the lags of that distance
+ * (gpoeo_pd_describe_plan then reports transforms of 4096 points).  Rolling
+ * detection always does, over its suffix windows.  A rigorous absolute error
+ * bound of each D_c(T), from the channel norms, decides which scores are within
+ * 1e-6 relative of the exact value; every other lag (exact zeros included) is recomputed as an fp64 sum
  * before the selection, which then proceeds as above.  Selections equal those
  * of the direct scores.  Requires a transform of at most 2^22 points: N + Tmax
  * <= 2^22, or N <= 2^22 with a head-tail transform of at most min(2^20, L / 2)
@@ -189,7 +194,9 @@ typedef struct {
                                  the (x[i], x[i+T]) pairs the definition of S(T) sums     */
     double pairs_scored;      /* pairs with T in [tmin, tmax] the score stage evaluates   */
     size_t workspace_bytes;   /* same as gpoeo_pd_workspace_bytes                          */
-    int64_t fft_len;          /* FFT scores: points per transform (0 otherwise)           */
+    int64_t fft_len;          /* FFT scores: points per transform (0 otherwise; 4096, less
+                                 than N + tmax and without a wrap term, for transforms of
+                                 sample blocks)                                          */
     int64_t fft_wrap_len;     /* FFT scores whose transform holds only N points: points
                                  of the head-tail transform of the wrap term; else 0      */
     int64_t fft_wrap_lags;    /* lags T > fft_len - N that carry the wrap term; else 0   */
@@ -236,8 +243,9 @@ int gpoeo_pd_detect(const gpoeo_pd_desc* desc, const float* x, float* scores,
  * concurrent streams, or from several threads) race and must be serialised by
  * the caller.  The array's contents on entry are ignored.
  * Returns GPOEO_PD_EINVAL as gpoeo_pd_detect does, GPOEO_PD_ETOOBIG when
- * gpoeo_pd_workspace_bytes(desc) exceeds GPOEO_PD_NOALLOC_MAX_WORKSPACE (both
- * before launching anything), GPOEO_PD_EHIP if the array cannot be located or
+ * the call needs more than GPOEO_PD_NOALLOC_MAX_WORKSPACE (gpoeo_pd_workspace_bytes,
+ * or for FFT scores by sample blocks that of the long transforms, which then
+ * take their place; both before launching anything), GPOEO_PD_EHIP if the array cannot be located or
  * a launch failed. */
 #define GPOEO_PD_NOALLOC_MAX_WORKSPACE ((size_t)64 << 20)
 

@@ -18,6 +18,25 @@ namespace {
 constexpr int64_t kTargetWaves = 40960;
 constexpr size_t kAlign = 256;
 
+// FFT scores from transforms of sample blocks (fft_blocks.hip) instead of one
+// transform of N + Tmax points (or of N, with the wrap term).  Measured, per
+// call, long transforms -> sample blocks: 1024 x 262144, T 32768 5.3 -> 3.6 ms;
+// 96 x 100003, T 12345 276 -> 222 us; 16 x 16384, T 4096 117 -> 78 us; 16 x
+// 262144, T 131072 610 -> 599 us.  Their sums over the blocks grow with Tmax
+// and win no longer past 2^17 lags (16 x 2^20, T 2^17 1.20 -> 1.20 ms, T 2^18
+// 1.78 -> 1.82 ms).  One to eight sequences would gain too (4 x 16384, T 4096
+// 117 -> 78 us), but the transform lengths and wrap term that
+// gpoeo_pd_describe_plan states for such calls are relied on; rolling
+// detection, which describes no plan, takes the blocks from one sequence on (one
+// window of 65536, T 8192: 307 -> 183 us), and for its suffix windows always.
+constexpr int64_t kBlocksMinSeqs = 9;
+constexpr int32_t kBlocksMaxLag = 1 << 17;
+// Spectra of one launch, at most: larger batches run in several.  Smaller
+// pieces were slower down to the size of the last-level cache and below (1024
+// x 262144: 3.55 ms a call in one piece, 3.7 ms in pieces of 1 GiB, 4.1 ms of
+// 192 MiB, 5.0 ms of 96 MiB).
+constexpr int64_t kBlocksChunkBytes = int64_t(4) << 30;
+
 }  // namespace
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -85,7 +104,11 @@ bool launches_fit(const Plan& p) {
     if (!fits(p.num_windows, 1024) || !fits(seqs, 256)) return false;
     if (p.fft) {
         if (!fits(2 * seqs, 256)) return false;
-        if (!p.fft_ragged) {   // uniform transforms: one workgroup per tile of each pair
+        if (p.fft_blocks) {
+            if (!fits(p.blk_pairs * std::max<int64_t>(p.blk_nb, p.blk_j), 512) ||
+                !fits(2 * p.blk_pairs * (kFftBlockSamples / 256) * ((p.blk_j + 15) / 16), 256))
+                return false;
+        } else {   // uniform transforms: one workgroup per tile of each pair
             const int64_t per_pair =
                 p.fft_m2 == 1 ? 1 : std::max<int64_t>(p.fft_m2 / p.fft_cols, p.fft_m1 / 2 + 1);
             if (p.fft_pairs > kMax / 256 / per_pair) return false;
@@ -110,8 +133,9 @@ bool launches_fit(const Plan& p) {
 }
 
 // ragged: the windows will come from a table (lengths up to d->n, Tmax up to
-// d->tmax); an FFT plan then sizes its transforms per pair (length classes).
-int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
+// d->tmax).  min_seqs: an FFT plan of fewer sequences keeps the long transforms.
+int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
+              int64_t min_seqs = kBlocksMinSeqs) {
     if (!d) return GPOEO_PD_EINVAL;
     if (d->reserved0 != 0 || d->reserved1 != 0) return GPOEO_PD_EINVAL;
     if (d->flags & ~(GPOEO_PD_SCORES_ONLY | GPOEO_PD_NO_RESCUE | GPOEO_PD_FFT_SCORES |
@@ -151,7 +175,7 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
     p->flags = d->flags;
 
     p->fft = (d->flags & GPOEO_PD_FFT_SCORES) != 0;
-    p->fft_ragged = p->fft && ragged;
+    p->fft_table = p->fft && ragged;
     if (p->fft) {
         // smallest power of two (at least 64) holding N + Tmax points
         int32_t lg = kFftMinLog2;
@@ -175,6 +199,16 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
             }
         }
         if (!set_fft_geometry(p, lg)) return GPOEO_PD_EINVAL;
+        p->fft_blocks =
+            ragged || (d->num_windows * (int64_t)d->num_channels >= min_seqs &&
+                       lg > kFftSmallTileLog2 && d->tmax <= kBlocksMaxLag);
+        if (p->fft_blocks) {
+            p->fft_wrap = false;
+            p->fft_log2 = kFftBlockLog2;
+            p->fft_len = kFftBlockPoints;
+            p->blk_nb = (int32_t)((d->n + kFftBlockSamples - 1) / kFftBlockSamples);
+            p->blk_j = (d->tmax + kFftBlockSamples - 1) / kFftBlockSamples;
+        }
     }
 
     p->lags_per_lane = choose_lags_per_lane(d->n, d->tmin, d->tmax);
@@ -256,6 +290,12 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
         p->lags_padded = p->lags;
         p->chunks = 1;
         p->fft_pairs = (bc + 1) / 2;
+        if (p->fft_blocks) {
+            const int64_t pair_bytes =
+                (int64_t)p->blk_nb * 2 * kFftBlockSamples * 2 * (int64_t)sizeof(double);
+            p->blk_pairs = std::min(p->fft_pairs,
+                                    std::max<int64_t>(1, kBlocksChunkBytes / pair_bytes));
+        }
     }
     p->mfma = mfma;
     p->mfma_table = mfma && ragged;
@@ -310,7 +350,7 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
             return GPOEO_PD_EINVAL;
     }
     if (n_part > (INT64_MAX / 16)) return GPOEO_PD_EINVAL;
-    int64_t n_fstat = 0, n_edge = 0, n_tw = 0, n_z = 0, n_cls = 0, n_zw = 0, n_wrap = 0;
+    int64_t n_fstat = 0, n_edge = 0, n_tw = 0, n_z = 0, n_zw = 0, n_wrap = 0;
     int64_t n_dig = 0, n_qstat = 0, n_rpart = 0;
     if (p->mfma &&
         (!mul_ok(bc, 4, &n_qstat) || !mul_ok(bc, 2 * ((int64_t)d->tmax + 1), &n_edge) ||
@@ -321,11 +361,14 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
          n_rpart > (INT64_MAX / 16)))
         return GPOEO_PD_EINVAL;
     if (p->fft) {
-        if (!mul_ok(bc, 4, &n_fstat) || !mul_ok(bc, 2 * ((int64_t)d->tmax + 1), &n_edge) ||
+        if (!mul_ok(bc, 4, &n_fstat) || !mul_ok(bc, (int64_t)d->tmax + 1, &n_edge) ||
             !mul_ok(p->fft_pairs, p->fft_len, &n_z) || n_z > (INT64_MAX / 64))
             return GPOEO_PD_EINVAL;
         n_tw = fft_twiddle_count(*p);
-        n_cls = fft_class_ints(*p);
+        if (p->fft_blocks) {   // spectra of the blocks and of the lag tiles
+            n_z = 2 * p->blk_pairs * p->blk_nb * kFftBlockSamples;
+            n_zw = 2 * p->blk_pairs * p->blk_j * kFftBlockSamples;
+        }
         if (p->fft_wrap &&
             (!mul_ok(2 * p->fft_pairs, int64_t(1) << p->fft_wrap_log2, &n_zw) ||
              n_zw > (INT64_MAX / 64) || !mul_ok(bc, p->fft_wrap_m, &n_wrap)))
@@ -348,14 +391,12 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false) {
     if (p->sliding) off = align_up(off + (size_t)n_part * sizeof(double));
     p->off_fstat = off;                           // FFT mode: per-sequence sums
     off = align_up(off + (size_t)n_fstat * sizeof(double));
-    p->off_edge = off;                            // head and tail sums of squares
+    p->off_edge = off;                            // energies of each lag's samples
     off = align_up(off + (size_t)n_edge * sizeof(double));
     p->off_tw = off;                              // twiddle tables (complex fp64)
     off = align_up(off + (size_t)n_tw * 2 * sizeof(double));
     p->off_z = off;                               // transforms (complex fp64)
     off = align_up(off + (size_t)n_z * 2 * sizeof(double));
-    p->off_cls = off;                             // length classes (ragged FFT plans)
-    off = align_up(off + (size_t)n_cls * sizeof(int32_t));
     p->off_zw = off;                              // head and tail transforms (wrap)
     off = align_up(off + (size_t)n_zw * 2 * sizeof(double));
     p->off_wrap = off;                            // wrap terms
@@ -433,19 +474,19 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
     if (!mark(1)) return GPOEO_PD_EHIP;
     if (p.fft) {
         char* ws = static_cast<char*>(workspace);
-        int32_t* cls = p.fft_ragged ? reinterpret_cast<int32_t*>(ws + p.off_cls) : nullptr;
-        double* zw = p.fft_wrap ? reinterpret_cast<double*>(ws + p.off_zw) : nullptr;
+        double* zw = p.fft_wrap || p.fft_blocks ? reinterpret_cast<double*>(ws + p.off_zw)
+                                                : nullptr;
         double* wrap = p.fft_wrap ? reinterpret_cast<double*>(ws + p.off_wrap) : nullptr;
         if (gpoeo::launch_fft_scores(p, x, fstat, reinterpret_cast<double*>(ws + p.off_edge),
                                      reinterpret_cast<double*>(ws + p.off_tw),
-                                     reinterpret_cast<double*>(ws + p.off_z), c.part, cls, zw,
+                                     reinterpret_cast<double*>(ws + p.off_z), c.part, zw,
                                      wrap, c.s64, scores, w.w[0], stream) != hipSuccess)
             return GPOEO_PD_EHIP;
         if (!mark(2)) return GPOEO_PD_EHIP;
         if ((!gpoeo::fft_fused_finalize(p, scores != nullptr) &&
              gpoeo::launch_finalize(p, w, c.part, c.s64, scores, stream) != hipSuccess) ||
             gpoeo::launch_select_init(p, c.sb, stream) != hipSuccess ||
-            gpoeo::launch_fft_fixup(p, w, x, fstat, cls, c.s64, scores, c.sb, stream) !=
+            gpoeo::launch_fft_fixup(p, w, x, fstat, c.s64, scores, c.sb, stream) !=
                 hipSuccess)
             return GPOEO_PD_EHIP;
     } else if (p.mfma) {
@@ -497,9 +538,9 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
 
 int detect_impl(const gpoeo_pd_desc* desc, const float* x, float* scores,
                 gpoeo_pd_result* results, void* workspace, size_t workspace_bytes,
-                hipStream_t stream, hipEvent_t* ev) {
+                hipStream_t stream, hipEvent_t* ev, int64_t min_seqs = gpoeo::kBlocksMinSeqs) {
     gpoeo::Plan p;
-    const int rc = gpoeo::make_plan(desc, &p);
+    const int rc = gpoeo::make_plan(desc, &p, false, min_seqs);
     if (rc != GPOEO_PD_OK) return rc;
     const bool scores_only = (p.flags & GPOEO_PD_SCORES_ONLY) != 0;
     if (!x || (!results && !scores_only) || !workspace) return GPOEO_PD_EINVAL;
@@ -533,7 +574,7 @@ int make_rolling(const gpoeo_pd_desc* d, const gpoeo_pd_rolling_params* rp, Roll
     if (!(span < GPOEO_PD_ROLLING_MAX)) return GPOEO_PD_EINVAL;
     const int32_t jmax = span < 0.0 ? 1 : (int32_t)std::floor(span) + 2;
     if (jmax > GPOEO_PD_ROLLING_MAX) return GPOEO_PD_EINVAL;
-    int rc = gpoeo::make_plan(d, &r->a);
+    int rc = gpoeo::make_plan(d, &r->a, false, 1);
     if (rc != GPOEO_PD_OK) return rc;
     gpoeo_pd_desc dc = *d;
     if (d->num_windows > INT32_MAX / jmax) return GPOEO_PD_EINVAL;
@@ -654,6 +695,33 @@ int gpoeo_pd_detect_staged(const gpoeo_pd_desc* desc, const float* x, float* sco
 }
 
 }  // extern "C"
+
+namespace gpoeo {
+
+int detect_within(const gpoeo_pd_desc* desc, const float* x, float* scores,
+                  gpoeo_pd_result* results, void* workspace, size_t workspace_bytes,
+                  hipStream_t stream) {
+    Plan p;
+    int rc = make_plan(desc, &p);
+    if (rc != GPOEO_PD_OK) return rc;
+    return detect_impl(desc, x, scores, results, workspace, workspace_bytes, stream, nullptr,
+                       p.bytes <= workspace_bytes ? kBlocksMinSeqs : INT64_MAX);
+}
+
+int least_workspace(const gpoeo_pd_desc* desc, size_t* bytes) {
+    Plan p;
+    int rc = make_plan(desc, &p);
+    if (rc != GPOEO_PD_OK) return rc;
+    *bytes = p.bytes;
+    if (p.fft_blocks) {
+        rc = make_plan(desc, &p, false, INT64_MAX);
+        if (rc != GPOEO_PD_OK) return rc;
+        *bytes = std::min(*bytes, p.bytes);
+    }
+    return GPOEO_PD_OK;
+}
+
+}  // namespace gpoeo
 
 extern "C" {
 

@@ -1,0 +1,446 @@
+// FFT scores of a batch from short transforms of sample blocks.
+//
+// r(T) = sum_i y_i y_{i+T} is needed only for T <= Tmax, a fraction of N, so the
+// sequence is cut into blocks x_b of m = 2048 samples and
+//   r(j m + n) = sum_b sum_{i<m} x_b(i) s_{b+j}(i + n),   0 < n <= m,
+// with s_b the 2m samples of blocks b and b + 1.  With X_b the 2m-point
+// transform of the zero-padded block, the transform of s_b is X_b(k) +
+// (-1)^k X_{b+1}(k), so that the spectrum of r over lags j m + 1 .. (j + 1) m is
+//   R_j(k) = C_j(k) + (-1)^k C_{j+1}(k),   C_j(k) = sum_b conj(X_b(k)) X_{b+j}(k).
+// Three launches do it:
+//   blocks_fwd_kernel   X_b of every block, one 4096-point transform a workgroup
+//   blocks_corr_kernel  C_j along the blocks, every frequency on its own
+//   blocks_inv_kernel   r of m lags from R_j, and their D(T)
+//
+// Against one transform of N + Tmax points split into columns and rows, the
+// spectra take two sweeps of 2N points instead of four of 2^k >= N + Tmax (or of
+// 2^k >= N and six of the head-tail transform), every access is a contiguous
+// run of at least 512 bytes, and N is padded to a multiple of 2048 instead of a
+// power of two.  The sums over the blocks cost 4 N Tmax / 2048 multiply-adds a
+// sequence, below the memory time up to Tmax of about 100,000.
+//
+// Measured on 1024 windows of 262,144 samples, T up to 32,768 (all three are
+// bound by memory; a 2 GiB copy runs at 4.9 TB/s): forward 1.08 ms for 5.4 GB,
+// block sums 1.15 ms for 4.8 GB, inverse 0.29 ms for 1.2 GB, where the long
+// transforms and their wrap term took 4.38 ms for 15.3 GB.
+#include <algorithm>
+#include <cmath>
+
+#include "fft_common.h"
+#include "internal.h"
+
+namespace gpoeo {
+namespace {
+
+constexpr int kP = kFftBlockPoints;          // 4096 points a transform
+constexpr int kM = kFftBlockSamples;         // 2048 samples a block
+constexpr int kT = 512;                      // threads of a transform, eight points each
+constexpr int kTw = kP / 2;                  // twiddles e^(-2 pi i e / 4096), e < 2048
+static_assert(kP == 8 * kT && kP == 2 * kM && kT == 8 * kWave, "four radix-8 passes");
+
+struct BlockArgs {
+    FftArgs f;                 // x, fstat, edge, part, s64, scores, layout (f.lg = log2 kP)
+    // The entry t + 512 r of a spectrum, r < 4, is the frequency thread t of a
+    // transform ends with (Lanes): all of them below 2048 once.
+    double2* z;                // [2 pairs of this launch][nb][kM]: 2 X_b(k) of each sequence
+    double2* r;                // [2 pairs of this launch][jmax][kM]: 4 R_j(k)
+    int64_t pair0;             // first pair of this launch
+    int32_t nb, jmax;          // blocks and lag tiles of the longest window
+    int32_t step;              // workgroups per pair of the forward launch
+};
+
+// Samples, blocks and lag tiles of sequence s (none for an empty slot or past
+// the last sequence).
+struct Span {
+    int64_t n;
+    int32_t nb, j;
+};
+__device__ __forceinline__ Span span_of(const FftArgs& a, int64_t s) {
+    Span v = {0, 0, 0};
+    if (s >= a.seqs) return v;
+    const int64_t b = s / a.num_channels;
+    v.n = table_n(a.tab, b, a.n_all);
+    if (v.n <= 0) return v;
+    v.nb = (int32_t)((v.n + kM - 1) / kM);
+    v.j = (int32_t)((min(table_tmax(a.tab, b, a.tmax), a.tmax) + kM - 1) / kM);
+    return v;
+}
+
+// Eight-point transforms in registers, y_m = sum_r v_r W^(r m), W = e^(-2 pi i / 8)
+// (or its conjugate), natural order in and out; kHalf: v_4 .. v_7 are zero.
+template <bool kInverse, bool kHalf>
+__device__ __forceinline__ void dft8(double2 (&v)[8]) {
+    constexpr double c = 0.70710678118654752440;
+    auto turn = [](double2 z) {   // z times -i (forward) or i
+        return kInverse ? make_double2(-z.y, z.x) : make_double2(z.y, -z.x);
+    };
+    auto w1 = [&](double2 z) {    // z W
+        return kInverse ? make_double2((z.x - z.y) * c, (z.x + z.y) * c)
+                        : make_double2((z.x + z.y) * c, (z.y - z.x) * c);
+    };
+    const double2 a0 = kHalf ? v[0] : cadd(v[0], v[4]), a1 = kHalf ? v[0] : csub(v[0], v[4]);
+    const double2 a2 = kHalf ? v[2] : cadd(v[2], v[6]), a3 = turn(kHalf ? v[2] : csub(v[2], v[6]));
+    const double2 b0 = kHalf ? v[1] : cadd(v[1], v[5]), b1 = kHalf ? v[1] : csub(v[1], v[5]);
+    const double2 b2 = kHalf ? v[3] : cadd(v[3], v[7]), b3 = turn(kHalf ? v[3] : csub(v[3], v[7]));
+    const double2 e0 = cadd(a0, a2), e2 = csub(a0, a2), e1 = cadd(a1, a3), e3 = csub(a1, a3);
+    const double2 o0 = cadd(b0, b2), o2 = turn(csub(b0, b2));
+    const double2 o1 = w1(cadd(b1, b3)), o3 = turn(w1(csub(b1, b3)));
+    v[0] = cadd(e0, o0);
+    v[4] = csub(e0, o0);
+    v[1] = cadd(e1, o1);
+    v[5] = csub(e1, o1);
+    v[2] = cadd(e2, o2);
+    v[6] = csub(e2, o2);
+    v[3] = cadd(e3, o3);
+    v[7] = csub(e3, o3);
+}
+
+// The twiddles of a radix-8 pass, w^m for m = 1 .. 7: w, w^2 and w^4 from the
+// table (w = W_4096^e), the others as products of two of them or of one and a
+// product, each within the twiddle error 16 u that fft_bound assumes.
+struct Twiddles {
+    double2 w1, w2, w4;
+    __device__ __forceinline__ void load(const double2* __restrict__ tw, int e) {
+        w1 = tw[e];
+        w2 = tw[2 * e];
+        w4 = tw[4 * e];
+    }
+};
+template <bool kInverse>
+__device__ __forceinline__ void twiddle8(double2 (&v)[8], const Twiddles& t) {
+    const double2 w3 = cmul(t.w1, t.w2), w5 = cmul(t.w1, t.w4), w6 = cmul(t.w2, t.w4);
+    const double2 w7 = cmul(w3, t.w4);
+    auto mul = [](double2 z, double2 w) { return kInverse ? cmul_conj(z, w) : cmul(z, w); };
+    v[1] = mul(v[1], t.w1);
+    v[2] = mul(v[2], t.w2);
+    v[3] = mul(v[3], w3);
+    v[4] = mul(v[4], t.w4);
+    v[5] = mul(v[5], w5);
+    v[6] = mul(v[6], w6);
+    v[7] = mul(v[7], w7);
+}
+
+// LDS slots of point i, one free slot after every 8 and one more after every
+// 64: each of the accesses below then touches all banks evenly.  Thread t =
+// 64 w + c, c = 8 p + q, holds eight points a pass (r = 0 .. 7):
+//   pass 1  t + 512 r               pass 2  512 w + c + 64 r
+//   pass 3  512 w + 64 p + q + 8 r  pass 4  512 w + 8 c + r
+// (decimation in frequency: 4096 natural points in, frequency w + 8 p + 64 q +
+// 512 r of the point at 512 w + 64 p + 8 q + r out), so passes 2 to 4 exchange
+// points inside a wavefront only.
+constexpr int kSlots = kP + kP / 8 + kP / 64;
+struct Lanes {
+    int t, s1, s2, s3, s4, sk, sm;
+    __device__ __forceinline__ Lanes() {
+        t = (int)threadIdx.x;
+        const int w = t >> 6, c = t & 63, p = c >> 3, q = c & 7;
+        s1 = t + (t >> 3) + (t >> 6);            // + 584 r
+        s2 = 584 * w + c + p;                    // + 73 r
+        s3 = 584 * w + 73 * p + q;               // + 9 r
+        s4 = 584 * w + 9 * c + p;                // + r
+        // slots of this thread's frequencies k = w + 8 p + 64 q + 512 r, and of
+        // their mirrors 4096 - k (for thread 0, whose k = 0 is no mirror of
+        // another, from r = 1 on)
+        sk = w + 9 * p + 73 * q;                 // + 584 r
+        const int u = kT - (w + 8 * p + 64 * q);
+        sm = u + (u >> 3) + (u >> 6);            // + 584 (7 - r)
+    }
+};
+template <int kStep>
+__device__ __forceinline__ void put8(double2* lds, int s, const double2 (&v)[8]) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) lds[s + kStep * r] = v[r];
+}
+template <int kStep>
+__device__ __forceinline__ void get8(const double2* lds, int s, double2 (&v)[8]) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = lds[s + kStep * r];
+}
+// Orders this wavefront's LDS writes before its next reads (its LDS operations
+// run in order; no other wavefront's points are involved).
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Workgroups of a forward launch (two fit a CU), if there are as many blocks
+// (1024 to 8192 differ by 3% on 1024 x 262144 and 256 x 8 x 131072).
+constexpr int64_t kFwdGroups = 4096;
+
+// Transforms of blocks of a pair (a, b): z = y_a + i y_b, then the two spectra
+// 2 A(k) = Z(k) + conj Z(P - k), 2 B(k) = (Z(k) - conj Z(P - k)) / i for k <
+// 2048; the entry of k = 0 holds the two real values at k = 0 and k = 2048.  A
+// workgroup takes every step-th block; the next one's samples are loaded while
+// this one is transformed and the twiddles stay on chip (1.39 -> 1.08 ms on the
+// batch above; 1.83 ms before the mirror exchange was halved to the upper four
+// values).
+__global__ __launch_bounds__(kT, 4) void blocks_fwd_kernel(BlockArgs a) {
+    __shared__ double2 lds[kSlots];
+    const int64_t pl = blockIdx.x / a.step;                       // pair within the launch
+    const int64_t sa = 2 * (a.pair0 + pl), sb = sa + 1;
+    const Seq qa = seq_of(a.f, sa), qb = seq_of(a.f, sb);
+    const int32_t na = span_of(a.f, sa).nb, nbb = span_of(a.f, sb).nb;
+    const int32_t nb = max(na, nbb);
+    const Lanes at;
+    const int c = at.t & 63;
+    float xa[4], xb[4];
+    auto samples = [&](int32_t b) {
+        const int64_t i0 = (int64_t)b * kM + at.t;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = i0 + kT * r;
+            xa[r] = i < qa.n ? qa.p[i] : 0.0f;
+            xb[r] = i < qb.n ? qb.p[i] : 0.0f;
+        }
+    };
+    int32_t b = (int32_t)(blockIdx.x % a.step);
+    if (b >= nb) return;
+    samples(b);
+    // the first pass's twiddles stay in registers, W_512^e for the others in LDS
+    // (ordered before its first reads by the first pass's barrier)
+    __shared__ double2 tw512[256];
+    Twiddles t1;
+    t1.load(a.f.tw, at.t);
+    if (at.t < 256) tw512[at.t] = a.f.tw[8 * at.t];
+    while (true) {
+        double2 v[8];
+        const int64_t i0 = (int64_t)b * kM + at.t;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = i0 + kT * r;
+            v[r] = make_double2(i < qa.n ? (double)xa[r] - qa.mu : 0.0,
+                                i < qb.n ? (double)xb[r] - qb.mu : 0.0);
+        }
+        const int32_t next = b + a.step;
+        if (next < nb) samples(next);
+        dft8<false, true>(v);
+        twiddle8<false>(v, t1);
+        put8<584>(lds, at.s1, v);
+        __syncthreads();
+        Twiddles tw;
+        tw.load(tw512, c);
+        get8<73>(lds, at.s2, v);
+        dft8<false, false>(v);
+        twiddle8<false>(v, tw);
+        put8<73>(lds, at.s2, v);
+        wave_exchange();
+        tw.load(tw512, 8 * (c & 7));
+        get8<9>(lds, at.s3, v);
+        dft8<false, false>(v);
+        twiddle8<false>(v, tw);
+        put8<9>(lds, at.s3, v);
+        wave_exchange();
+        get8<1>(lds, at.s4, v);
+        dft8<false, false>(v);
+        __syncthreads();                                          // all points read
+#pragma unroll
+        for (int r = 4; r < 8; ++r) lds[at.sk + 584 * r] = v[r];
+        __syncthreads();
+        double2* __restrict__ za = a.z + ((2 * pl) * a.nb + b) * (int64_t)kM + at.t;
+        double2* __restrict__ zb = za + (int64_t)a.nb * kM;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool edge = r == 0 && at.t == 0;                // k = 0, with k = 2048
+            const double2 zk = v[r];
+            const double2 zm = lds[edge ? 584 * 4 : at.sm + 584 * (7 - r)];
+            double2 va = make_double2(zk.x + zm.x, zk.y - zm.y);
+            double2 vb = make_double2(zk.y + zm.y, zm.x - zk.x);
+            if (edge) {
+                va = make_double2(2.0 * zk.x, 2.0 * zm.x);
+                vb = make_double2(2.0 * zk.y, 2.0 * zm.y);
+            }
+            if (b < na) za[kT * r] = va;
+            if (b < nbb) zb[kT * r] = vb;
+        }
+        if (next >= nb) break;
+        b = next;
+        __syncthreads();                                          // all mirrors read
+    }
+}
+
+// C_j0 .. C_{j0+kJ} of one sequence and frequency a thread, then R_j.  The
+// spectra of consecutive blocks stream through a ring of registers, kAhead of
+// them loaded before they are needed.  With more than kJ lag tiles (kOffset) a
+// workgroup takes kJ of them, from j0 = kJ blockIdx.y on, and block b's own
+// spectrum is a second stream.  Entry 0's two real values are multiplied
+// separately (p, q below).
+constexpr int kCorrThreads = 256;
+template <int kJ, bool kOffset>
+__global__ __launch_bounds__(kCorrThreads) void blocks_corr_kernel(BlockArgs a) {
+    constexpr int kAhead = kOffset ? 2 : 3;
+    constexpr int kRing = kJ + 1 + kAhead;
+    constexpr int kParts = kM / kCorrThreads;
+    const int64_t sl = blockIdx.x / kParts;
+    const Span sp = span_of(a.f, 2 * a.pair0 + sl);
+    const int32_t j0 = kOffset ? kJ * (int32_t)blockIdx.y : 0;
+    if (j0 >= sp.j) return;
+    const int k = (int)(blockIdx.x % kParts) * kCorrThreads + (int)threadIdx.x;
+    const double2* __restrict__ zp = a.z + sl * a.nb * (int64_t)kM + k;
+    const bool real2 = k == 0;
+    auto spectrum = [&](int32_t b) {
+        return b < sp.nb ? zp[(int64_t)b * kM] : make_double2(0.0, 0.0);
+    };
+    double2 ring[kRing], acc[kJ + 1];
+#pragma unroll
+    for (int i = 0; i <= kJ; ++i) acc[i] = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) ring[i] = spectrum(j0 + i);
+    double2 own = kOffset ? spectrum(0) : make_double2(0.0, 0.0);
+    const int32_t last = sp.nb - j0;      // blocks past it have no partner
+    for (int32_t b0 = 0; b0 < last; b0 += kRing) {
+#pragma unroll
+        for (int u = 0; u < kRing; ++u) {
+            const int32_t b = b0 + u;
+            if (b < last) {               // the same for every thread
+                const double2 x = kOffset ? own : ring[u];
+                if (kOffset) own = spectrum(b + 1);
+                const double p = real2 ? 0.0 : x.y, q = real2 ? x.y : x.x, h = real2 ? 0.0 : -x.y;
+#pragma unroll
+                for (int j = 0; j <= kJ; ++j) {
+                    const double2 y = ring[(u + j) % kRing];
+                    acc[j].x = fma(x.x, y.x, acc[j].x);
+                    acc[j].y = fma(q, y.y, acc[j].y);
+                    acc[j].x = fma(p, y.y, acc[j].x);
+                    acc[j].y = fma(h, y.x, acc[j].y);
+                }
+                ring[u] = spectrum(b + j0 + kRing);
+            }
+        }
+    }
+    // entry k holds a frequency of parity w = k / 64 (mod 8)
+    const double sign = (k & 64) ? -1.0 : 1.0;
+    double2* __restrict__ out = a.r + (sl * a.jmax + j0) * (int64_t)kM + k;
+#pragma unroll
+    for (int j = 0; j < kJ; ++j)
+        if (j0 + j < sp.j)
+            out[(int64_t)j * kM] = make_double2(fma(sign, acc[j + 1].x, acc[j].x),
+                                                fma(sign, acc[j + 1].y, acc[j].y));
+}
+
+// r(T) of both sequences of a pair for one tile of lags: Q = R_a + i R_b over
+// all 4096 frequencies, its inverse transform (the passes of the forward one
+// backwards), and D(T) for T = 2048 j + n, 0 < n <= 2048.  The energies of
+// those lags are loaded before the transform (0.32 -> 0.29 ms).
+__global__ __launch_bounds__(kT, 4) void blocks_inv_kernel(BlockArgs a) {
+    __shared__ double2 lds[kSlots];
+    const int64_t pl = blockIdx.x / a.jmax;
+    const int32_t j = (int32_t)(blockIdx.x % a.jmax);
+    const int64_t sa = 2 * (a.pair0 + pl), sb = sa + 1;
+    const Span pa = span_of(a.f, sa), pb = span_of(a.f, sb);
+    if (j >= max(pa.j, pb.j)) return;
+    const Lanes at;
+    const int c = at.t & 63;
+    const double2* __restrict__ ra = a.r + ((2 * pl) * a.jmax + j) * (int64_t)kM + at.t;
+    const double2* __restrict__ rb = ra + (int64_t)a.jmax * kM;
+    double2 va[4], vb[4], v[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        va[r] = j < pa.j ? ra[kT * r] : make_double2(0.0, 0.0);
+        vb[r] = j < pb.j ? rb[kT * r] : make_double2(0.0, 0.0);
+    }
+    Twiddles t3, t2, t1;
+    t3.load(a.f.tw, 64 * (c & 7));
+    t2.load(a.f.tw, 8 * c);
+    t1.load(a.f.tw, at.t);
+    const int64_t t0 = (int64_t)j * kM + at.t;
+    // lags t0 + 512 r, r < 4 (n = 0 is another tile's: thread 0 takes n = 2048
+    // in its place)
+    auto lag_of = [&](int r) { return r == 0 && at.t == 0 ? t0 + kM : t0 + kT * r; };
+    double ea[4], eb[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        ea[r] = lag_energy(a.f, sa, lag_of(r));
+        eb[r] = lag_energy(a.f, sb, lag_of(r));
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool edge = r == 0 && at.t == 0;
+        double2 qm = make_double2(va[r].x + vb[r].y, vb[r].x - va[r].y);
+        v[r] = make_double2(va[r].x - vb[r].y, va[r].y + vb[r].x);
+        if (edge) {                                               // k = 0 and k = 2048
+            v[r] = make_double2(va[r].x, vb[r].x);
+            qm = make_double2(va[r].y, vb[r].y);
+        }
+        lds[edge ? 584 * 4 : at.sm + 584 * (7 - r)] = qm;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 4; r < 8; ++r) v[r] = lds[at.sk + 584 * r];
+    dft8<true, false>(v);
+    __syncthreads();                                              // all mirrors read
+    put8<1>(lds, at.s4, v);
+    wave_exchange();
+    get8<9>(lds, at.s3, v);
+    twiddle8<true>(v, t3);
+    dft8<true, false>(v);
+    put8<9>(lds, at.s3, v);
+    wave_exchange();
+    get8<73>(lds, at.s2, v);
+    twiddle8<true>(v, t2);
+    dft8<true, false>(v);
+    put8<73>(lds, at.s2, v);
+    __syncthreads();
+    get8<584>(lds, at.s1, v);
+    twiddle8<true>(v, t1);
+    dft8<true, false>(v);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double2 y = r == 0 && at.t == 0 ? v[4] : v[r];
+        write_lag(a.f, sa, lag_of(r), ea[r], y.x);
+        write_lag(a.f, sb, lag_of(r), eb[r], y.y);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const float* x,
+                             const double* fstat, double* edge, double* part, double* s64,
+                             float* scores, float w0, hipStream_t s) {
+    BlockArgs a = {};
+    a.f.x = x;
+    a.f.fstat = fstat;
+    a.f.edge = edge;
+    a.f.tw = reinterpret_cast<const double2*>(u.tw);
+    a.f.part = part;
+    a.f.seqs = p.num_windows * (int64_t)p.num_channels;
+    a.f.n_all = p.n;
+    a.f.window_stride = p.window_stride;
+    a.f.channel_stride = p.channel_stride;
+    a.f.num_channels = p.num_channels;
+    a.f.tmin = p.tmin;
+    a.f.tmax = p.tmax;
+    a.f.lags = p.lags;
+    a.f.tab = p.table;
+    a.f.lg = kFftBlockLog2;
+    a.f.len = kP;
+    a.f.s64 = s64;
+    a.f.scores = scores;
+    a.f.w0 = w0;
+    a.z = reinterpret_cast<double2*>(u.z);
+    a.r = reinterpret_cast<double2*>(u.r);
+    a.nb = p.blk_nb;
+    a.jmax = p.blk_j;
+    for (int64_t p0 = 0; p0 < p.fft_pairs; p0 += p.blk_pairs) {
+        const int64_t pc = std::min(p.blk_pairs, p.fft_pairs - p0);
+        a.pair0 = p0;
+        a.step = (int32_t)std::min<int64_t>(p.blk_nb, (kFwdGroups + pc - 1) / pc);
+        hipLaunchKernelGGL(blocks_fwd_kernel, dim3((unsigned)(pc * a.step)), dim3(kT), 0, s, a);
+        const dim3 grid((unsigned)(2 * pc * (kM / kCorrThreads))), block(kCorrThreads);
+        if (p.blk_j > 16)
+            hipLaunchKernelGGL((blocks_corr_kernel<16, true>),
+                               dim3(grid.x, (unsigned)((p.blk_j + 15) / 16)), block, 0, s, a);
+        else if (p.blk_j > 8)
+            hipLaunchKernelGGL((blocks_corr_kernel<16, false>), grid, block, 0, s, a);
+        else if (p.blk_j > 4)
+            hipLaunchKernelGGL((blocks_corr_kernel<8, false>), grid, block, 0, s, a);
+        else if (p.blk_j > 2)
+            hipLaunchKernelGGL((blocks_corr_kernel<4, false>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((blocks_corr_kernel<2, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL(blocks_inv_kernel, dim3((unsigned)(pc * a.jmax)), dim3(kT), 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace gpoeo

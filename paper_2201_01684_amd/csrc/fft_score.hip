@@ -29,8 +29,9 @@
 #include <algorithm>
 #include <cmath>
 
-#include "internal.h"
 #include "exact.h"
+#include "fft_common.h"
+#include "internal.h"
 
 namespace gpoeo {
 namespace {
@@ -39,71 +40,6 @@ constexpr int kThreads = 256;                          // edge and fix-up kernel
 constexpr int kTThreads = 1 << kFftThreadsLog2;        // transform kernels
 
 
-struct FftArgs {
-    const float* x;
-    const double* fstat;       // [S][4]: mean, sum y^2, sum |y|, unused (window statistics)
-    double* edge;              // [S][2][tmax + 1]: head and tail sums of y^2
-    const double2* tw;         // twiddle tables
-    double2* z;                // [pairs][len]
-    double* part;              // [S][lags]: D(T)
-    double* amp;               // spectra: [S][len/2 + 1] amplitudes |X_s(k)|
-    int64_t seqs;              // S = B * C
-    int64_t n_all, window_stride, channel_stride;
-    int64_t len;
-    int64_t tw_a, tw_b, tw_lo, tw_hi;
-    int32_t num_channels;
-    int32_t tmin, tmax, lags;
-    int32_t lg, lg1, lg2, lgc, lgr;
-    WindowTable tab;
-    // Ragged launches (windows of different lengths) transform the pairs of
-    // one length class, list[bounds[cls] .. bounds[cls + 1]) (class = log2 of
-    // the transform length).  Transform z of pair p sits at z + p * zstride.
-    const int32_t* list;
-    const int32_t* bounds;
-    int64_t zstride;
-    int32_t cls;
-    // Loads of a transform see samples [seg_start, seg_start + seg_len) of
-    // each sequence (seg_len 0: all of it): the heads and tails of the wrap
-    // correction.
-    int64_t seg_start, seg_len;
-    // Wrap correction: the inverse column kernel of the head-tail transform
-    // writes the cross-correlations cc(s), s < wm, to wout ([S][wm]); the one
-    // of the main transform subtracts wrap[s][Tmax - T] from r(T) for T > wrap_w.
-    double* wout;
-    const double* wrap;
-    int64_t wrap_w;
-    int32_t wm;
-    // Fused finalisation (one channel, uniform batch): S(T) to s64 and scores.
-    double* s64;
-    float* scores;
-    float w0;
-};
-
-// Transform kernels come in two forms: uniform (kRagged false: one workgroup
-// per item, grid = items, the loop below runs once) and ragged (a capped grid
-// whose workgroups loop over the items of one length class).
-template <bool kRagged>
-__device__ __forceinline__ int64_t work_items(const FftArgs& a, int64_t per_pair) {
-    return kRagged ? (int64_t)(a.bounds[a.cls + 1] - a.bounds[a.cls]) * per_pair
-                   : (int64_t)gridDim.x;
-}
-template <bool kRagged>
-__device__ __forceinline__ int64_t pair_at(const FftArgs& a, int64_t k) {
-    return kRagged ? (int64_t)a.list[a.bounds[a.cls] + k] : k;
-}
-
-__device__ __forceinline__ double2 cadd(double2 a, double2 b) {
-    return make_double2(a.x + b.x, a.y + b.y);
-}
-__device__ __forceinline__ double2 csub(double2 a, double2 b) {
-    return make_double2(a.x - b.x, a.y - b.y);
-}
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 cmul_conj(double2 a, double2 b) {   // a * conj(b)
-    return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
 __device__ __forceinline__ uint32_t bitrev(uint32_t v, int lg) {
     return lg == 0 ? 0u : (__builtin_bitreverse32(v) >> (32 - lg));
 }
@@ -277,97 +213,46 @@ __device__ __forceinline__ double2 power_pair(double2 zk, double2 zm) {
     return make_double2(ux * ux + uy * uy, vx * vx + vy * vy);
 }
 
-struct Seq {
-    const float* p;
-    int64_t n;
-    double mu;
-};
-
-__device__ __forceinline__ Seq seq_of(const FftArgs& a, int64_t s) {
-    Seq q;
-    if (s >= a.seqs) {
-        q.p = nullptr;
-        q.n = 0;
-        q.mu = 0.0;
-        return q;
-    }
-    const int64_t b = s / a.num_channels;
-    const int64_t c = s % a.num_channels;
-    q.n = table_n(a.tab, b, a.n_all);
-    q.p = a.x + table_off(a.tab, b, a.window_stride) + c * a.channel_stride;
-    q.mu = a.fstat[4 * s];
-    if (a.seg_len > 0) {
-        q.p += a.seg_start;
-        q.n = min(q.n - a.seg_start, a.seg_len);
-    }
-    return q;
-}
-
-__device__ __forceinline__ double centred(const Seq& q, int64_t i) {
-    return i < q.n ? (double)q.p[i] - q.mu : 0.0;
-}
-
-// D(T) of sequence s from the scaled inverse transform value w = 4 L r(T).
-__device__ __forceinline__ void write_d(const FftArgs& a, int64_t s, int64_t t, double w) {
-    if (s >= a.seqs || t < a.tmin || t > a.tmax) return;
-    const int64_t b = s / a.num_channels;
-    const int64_t n = table_n(a.tab, b, a.n_all);
-    const bool live = n > 0 && t <= table_tmax(a.tab, b, a.tmax);
-    double d = 0.0;
-    if (live) {
-        double r = ldexp(w, -(a.lg + 2));
-        if (a.wrap && t > a.wrap_w) r -= a.wrap[s * a.wm + (a.tmax - t)];   // circular term
-        const double e = a.fstat[4 * s + 1];
-        const double* ed = a.edge + s * 2 * (int64_t)(a.tmax + 1);
-        d = ((e - ed[a.tmax + 1 + t]) + (e - ed[t])) - 2.0 * r;
-    }
-    const int64_t k = s * a.lags + (t - a.tmin);
-    if (a.s64) {   // the finalisation of a single channel, in its own arithmetic
-        if (!live && !a.scores) return;   // past a table window's lags: left unwritten
-        const double v = 0.0 + (double)a.w0 * (d / (double)(n - t));
-        a.s64[k] = v;
-        if (a.scores) a.scores[k] = (float)v;
-    } else {
-        a.part[k] = d;
-    }
-}
-
-// Sums of y^2 over the first T samples (head) and the last T samples (tail)
-// of a sequence, T = 0..Tmax of its window; one workgroup per (sequence,
-// side).  Tiles of 4096 terms are loaded (all of a thread's loads in flight at
-// once) and staged in LDS; each thread adds 16 consecutive terms, an
-// exclusive scan of the thread totals (lane shuffles within each wavefront,
-// then the wavefront totals in order) gives each thread its offset, and the
-// running sums go back through LDS for coalesced stores.  (The mean, sum y^2
-// and sum |y| come from the window statistics, computed with the same mean.)
+// Energies of the first and the last N - T samples of a sequence, E1(T) + E2(T)
+// = (E - tail(T)) + (E - head(T)) for T = 0..Tmax of its window, with head and
+// tail the sums of y^2 over the first and the last T samples; one workgroup per
+// sequence, half of its threads a side.  Tiles of 4096 terms a side are loaded
+// (all of a thread's loads in flight at once) and staged in LDS; each thread
+// adds 16 consecutive terms, an exclusive scan of the side's thread totals
+// (lane shuffles within each wavefront, then the wavefront totals in order)
+// gives each thread its offset, and the running sums of both sides go through
+// LDS for coalesced stores of their combination.  (The mean and E come from the
+// window statistics, computed with the same mean.)
 constexpr int kEdgeTile = 4096;
 constexpr int kEdgePer = kEdgeTile / kThreads;   // 16 terms per thread
 constexpr int kEdgeWaves = kThreads / kWave;
 
 __device__ __forceinline__ int edge_slot(int k) { return k + (k >> 4); }   // padded: no bank clash
 
-__global__ __launch_bounds__(kThreads) void fft_edge_kernel(FftArgs a) {
-    __shared__ double tile[kEdgeTile + kEdgeTile / 16];
-    __shared__ double wsum[kEdgeWaves];
-    const int64_t s = blockIdx.x >> 1;
-    const int side = blockIdx.x & 1;
+__global__ __launch_bounds__(2 * kThreads) void fft_edge_kernel(FftArgs a) {
+    __shared__ double tiles[2][kEdgeTile + kEdgeTile / 16];
+    __shared__ double wsum[2][kEdgeWaves];
+    const int64_t s = blockIdx.x;
+    const int side = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
+    double* tile = tiles[side];
     const int64_t b = s / a.num_channels;
     const int64_t c = s % a.num_channels;
     const int64_t n = table_n(a.tab, b, a.n_all);
+    if (n <= 0) return;
     const float* __restrict__ p = a.x + table_off(a.tab, b, a.window_stride) + c * a.channel_stride;
-    const double mu = a.fstat[4 * s];
-    double* __restrict__ out = a.edge + (s * 2 + side) * ((int64_t)a.tmax + 1);   // out[T]
-    // T = 0 .. this window's largest lag (nothing for an empty slot)
-    const int64_t span = n > 0 ? (int64_t)min(table_tmax(a.tab, b, a.tmax), a.tmax) + 1 : 1;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (threadIdx.x == 0) out[0] = 0.0;
+    const double mu = a.fstat[4 * s], e = a.fstat[4 * s + 1];
+    double* __restrict__ out = a.edge + s * ((int64_t)a.tmax + 1);   // out[T]
+    // T = 0 .. this window's largest lag
+    const int64_t span = (int64_t)min(table_tmax(a.tab, b, a.tmax), a.tmax) + 1;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    if (threadIdx.x == 0) out[0] = e + e;
     double carry = 0.0;
     // the next tile's samples are loaded while this tile is scanned
     float nxt[kEdgePer];
     auto load_tile = [&](int64_t k0, float (&v)[kEdgePer]) {
 #pragma unroll
         for (int r = 0; r < kEdgePer; ++r) {
-            const int64_t kk = k0 + (int)threadIdx.x + r * kThreads;
+            const int64_t kk = k0 + tid + r * kThreads;
             const bool in = kk < n && kk < span - 1;
             v[r] = in ? p[side == 0 ? kk : n - 1 - kk] : 0.0f;
         }
@@ -381,7 +266,7 @@ __global__ __launch_bounds__(kThreads) void fft_edge_kernel(FftArgs a) {
             if (k0 + kEdgeTile < span - 1) load_tile(k0 + kEdgeTile, nxt);
 #pragma unroll
             for (int r = 0; r < kEdgePer; ++r) {
-                const int k = (int)threadIdx.x + r * kThreads;
+                const int k = tid + r * kThreads;
                 const int64_t kk = k0 + k;
                 const double y = (kk < n && kk < span - 1) ? (double)v[r] - mu : 0.0;
                 tile[edge_slot(k)] = y * y;
@@ -389,30 +274,31 @@ __global__ __launch_bounds__(kThreads) void fft_edge_kernel(FftArgs a) {
         }
         __syncthreads();
         double part = 0.0;
-        for (int r = 0; r < kEdgePer; ++r) part += tile[edge_slot((int)threadIdx.x * kEdgePer + r)];
+        for (int r = 0; r < kEdgePer; ++r) part += tile[edge_slot(tid * kEdgePer + r)];
         double inc = part;   // inclusive scan within the wavefront
         for (int o = 1; o < kWave; o <<= 1) {
             const double u = __shfl_up(inc, o);
             if (lane >= o) inc += u;
         }
-        if (lane == kWave - 1) wsum[wave] = inc;
+        if (lane == kWave - 1) wsum[side][wave] = inc;
         __syncthreads();
         double run = carry, total = carry;
         for (int w = 0; w < kEdgeWaves; ++w) {
-            if (w < wave) run += wsum[w];
-            total += wsum[w];
+            if (w < wave) run += wsum[side][w];
+            total += wsum[side][w];
         }
         run += inc - part;   // this thread's exclusive offset
         for (int r = 0; r < kEdgePer; ++r) {
-            const int k = (int)threadIdx.x * kEdgePer + r;
+            const int k = tid * kEdgePer + r;
             run += tile[edge_slot(k)];
             tile[edge_slot(k)] = run;   // sum of terms 0 .. k0 + k: the value at T = k0 + k + 1
         }
         __syncthreads();
-        for (int r = 0; r < kEdgePer; ++r) {
-            const int k = (int)threadIdx.x + r * kThreads;
+        for (int r = 0; r < kEdgePer / 2; ++r) {
+            const int k = (int)threadIdx.x + r * 2 * kThreads;
             const int64_t t = k0 + k + 1;
-            if (t < span) out[t] = tile[edge_slot(k)];
+            if (t < span)
+                out[t] = (e - tiles[1][edge_slot(k)]) + (e - tiles[0][edge_slot(k)]);
         }
         carry = total;
         __syncthreads();
@@ -449,15 +335,11 @@ __global__ void fft_twiddle_kernel(double2* tw, int lga, int lgb, int lg, int lg
 }
 
 // Whole transform of one pair in one workgroup (L <= 2^12).
-template <int kTile, bool kRagged>
+template <int kTile>
 __global__ __launch_bounds__(kTThreads) void fft_single_kernel(FftArgs a) {
     constexpr int kRegPoints = (1 << kTile) / kTThreads;
     extern __shared__ double2 lds[];
-    const int64_t items = work_items<kRagged>(a, 1);
-    for (int64_t base = 0; base < items; base += gridDim.x) {
-    const int64_t item = base + blockIdx.x;
-    if (item >= items) break;
-    const int64_t pair = pair_at<kRagged>(a, item);
+    const int64_t pair = blockIdx.x;
     const Seq qa = seq_of(a, 2 * pair), qb = seq_of(a, 2 * pair + 1);
     const int lg = a.lg;
     const int len = 1 << lg;
@@ -500,24 +382,18 @@ __global__ __launch_bounds__(kTThreads) void fft_single_kernel(FftArgs a) {
         write_d(a, 2 * pair, t, lds[t].x);
         write_d(a, 2 * pair + 1, t, lds[t].y);
     }
-    if (!kRagged) break;
-    __syncthreads();   // the next pair reuses the LDS
-    }
 }
 
 // Split transform, step 1: column transforms (L1 points, stride L2) of
 // 2^lgc neighbouring columns, then the twiddles W_L^(k1 n2).  Row p of the
 // output holds frequency k1 = bitrev(p).
-template <int kTile, bool kRagged>
+template <int kTile>
 __global__ __launch_bounds__(kTThreads) void fft_cols_fwd_kernel(FftArgs a) {
     constexpr int kRegPoints = (1 << kTile) / kTThreads;
     extern __shared__ double2 lds[];
     const int64_t groups = int64_t(1) << (a.lg2 - a.lgc);
-    const int64_t items = work_items<kRagged>(a, groups);
-    for (int64_t base = 0; base < items; base += gridDim.x) {
-    const int64_t id = base + xcd_remap(blockIdx.x, gridDim.x);
-    if (id >= items) break;
-    const int64_t pair = pair_at<kRagged>(a, id / groups);
+    const int64_t id = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t pair = id / groups;
     const int64_t c0 = (id % groups) << a.lgc;
     const int cols = 1 << a.lgc;
     const int npts = (1 << a.lg1) * cols;
@@ -607,26 +483,20 @@ __global__ __launch_bounds__(kTThreads) void fft_cols_fwd_kernel(FftArgs a) {
         const int f = threadIdx.x + r * kTThreads;
         if (f < npts) zp[(int64_t)(f >> a.lgc) * l2 + c0 + (f & (cols - 1))] = cmul(lds[f], w[r]);
     }
-    if (!kRagged) break;
-    __syncthreads();   // the next item reuses the LDS
-    }
 }
 
 // Split transform, step 2: row k1 and its mirror row L1 - k1 (frequencies k
 // and L - k pair up between them): forward row transforms, separation into
 // the two sequences' power spectra, inverse row transforms, inverse twiddles.
 // A workgroup takes 2^lgr consecutive row pairs (4096 points in LDS).
-template <int kTile, bool kRagged>
+template <int kTile>
 __global__ __launch_bounds__(kTThreads) void fft_rows_kernel(FftArgs a) {
     constexpr int kRegPoints = (1 << kTile) / kTThreads;
     extern __shared__ double2 lds[];   // point i of slot q at i * 2^(lgr+1) + q
     const int64_t per = (int64_t(1) << (a.lg1 - 1)) + 1;   // row pairs per transform
     const int64_t wgs = (per + (1 << a.lgr) - 1) >> a.lgr;
-    const int64_t items = work_items<kRagged>(a, wgs);
-    for (int64_t base = 0; base < items; base += gridDim.x) {
-    const int64_t id = base + xcd_remap(blockIdx.x, gridDim.x);
-    if (id >= items) break;
-    const int64_t pair = pair_at<kRagged>(a, id / wgs);
+    const int64_t id = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t pair = id / wgs;
     const int64_t g0 = (id % wgs) << a.lgr;
     const uint32_t l1 = 1u << a.lg1;
     const int lgs = a.lgr + 1;                 // log2 of the slots
@@ -707,9 +577,6 @@ __global__ __launch_bounds__(kTThreads) void fft_rows_kernel(FftArgs a) {
         const uint32_t k1 = k1_of(q, valid, self);
         if (f >= npts || !valid || ((q & 1) && self)) continue;
         zp[(int64_t)bitrev(k1, a.lg1) * l2 + (f >> lgs)] = cmul_conj(lds[f], wv[r]);
-    }
-    if (!kRagged) break;
-    __syncthreads();   // the next item reuses the LDS
     }
 }
 
@@ -828,16 +695,13 @@ __global__ __launch_bounds__(kTThreads) void fft_wrap_rows_kernel(FftArgs a, int
 // Split transform, step 3: inverse column transforms (row p holds k1 =
 // bitrev(p): the bit-reversed input order of the decimation in time), and
 // D(T) for the lags T = n1 L2 + n2 in [tmin, tmax].
-template <int kTile, bool kRagged>
+template <int kTile>
 __global__ __launch_bounds__(kTThreads) void fft_cols_inv_kernel(FftArgs a) {
     constexpr int kRegPoints = (1 << kTile) / kTThreads;
     extern __shared__ double2 lds[];
     const int64_t groups = int64_t(1) << (a.lg2 - a.lgc);
-    const int64_t items = work_items<kRagged>(a, groups);
-    for (int64_t base = 0; base < items; base += gridDim.x) {
-    const int64_t id = base + xcd_remap(blockIdx.x, gridDim.x);
-    if (id >= items) break;
-    const int64_t pair = pair_at<kRagged>(a, id / groups);
+    const int64_t id = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t pair = id / groups;
     const int64_t c0 = (id % groups) << a.lgc;
     const int cols = 1 << a.lgc;
     const int npts = (1 << a.lg1) * cols;
@@ -878,9 +742,6 @@ __global__ __launch_bounds__(kTThreads) void fft_cols_inv_kernel(FftArgs a) {
             write_d(a, 2 * pair, t, lds[f].x);
             write_d(a, 2 * pair + 1, t, lds[f].y);
         }
-    }
-    if (!kRagged) break;
-    __syncthreads();   // the next item reuses the LDS
     }
 }
 
@@ -1060,6 +921,42 @@ __device__ double fft_bound_wrap(const double* fstat, int64_t s, int64_t seqs, i
     return 2.0 * (2.02 * (fwd + inv));
 }
 
+// The same for scores from transforms of sample blocks (P points, m samples a
+// block, nb blocks).  With zeta_b and y_b the norms of block b (of the pair and
+// of s), each separated spectrum errs by e1 sqrt(P) zeta_b; r comes from two
+// sums over b of products of two spectra, whose errors, summed over all
+// frequencies and divided by P, are at most 2 e1 zeta |y_a| + (e1 zeta)^2 each
+// (Cauchy-Schwarz over b); the fp64 sums (2 nb fused multiply-adds a component,
+// one more for R_j) add sqrt(2) gamma_{2 nb + 2} (|y_a| + e1 zeta)^2 each, and
+// the assembly R_a + i R_b one rounding of both.  The inverse transform adds phi
+// / sqrt(P) times the norm of R, at most the sum over b of the largest entry of
+// one spectrum, sqrt(m) y_b (Cauchy-Schwarz over its samples), times the norm of
+// the other, sqrt(P) times that of the samples of two blocks: phi sqrt(2 m)
+// |y_a|^2 (Cauchy-Schwarz over b), each norm enlarged by its error.
+__device__ double fft_bound_blocks(const double* fstat, int64_t s, int64_t seqs, int64_t n) {
+    const double u = 1.1102230246251565e-16;
+    const double ea = fstat[4 * s + 1];
+    const int64_t o = s ^ 1;
+    const double eb = o < seqs ? fstat[4 * o + 1] : 0.0;
+    const double ya = sqrt(ea), yb = sqrt(eb), zeta = sqrt(ea + eb);
+    const double nb = (double)((n + kFftBlockSamples - 1) / kFftBlockSamples);
+    const double mu = 16.0 * u;
+    const double g4 = 4.0 * u / (1.0 - 4.0 * u);
+    const double gs = (2.0 * nb + 2.0) * u / (1.0 - (2.0 * nb + 2.0) * u);
+    const double eta = mu + g4 * (1.4142135623730951 + mu);
+    const double keta = (double)(kFftBlockLog2 + 1) * eta;
+    const double phi = keta / (1.0 - keta);
+    const double e1 = phi + 4.0 * u;
+    const double pa = ya + 2.0 * e1 * zeta, pb = yb + 2.0 * e1 * zeta;
+    const double fwd = 2.0 * (2.0 * e1 * zeta * ya + e1 * e1 * zeta * zeta) +
+                       (2.0 * 1.4142135623730951 * gs + 2.0 * u) * pa * pa + 2.0 * u * pb * pb;
+    const double inv = phi * (1.0 + gs + g4) * sqrt(2.0 * (double)kFftBlockSamples) *
+                       (pa * pa + pb * pb);
+    const double k = 2.0 * (double)n + 2.0;
+    const double ge = k * u / (1.0 - k * u);
+    return 2.0 * (2.02 * (fwd + inv) + (2.0 * ge + 17.0 * u) * ea);
+}
+
 struct FixArgs {
     const float* x;
     const double* fstat;
@@ -1072,7 +969,7 @@ struct FixArgs {
     int32_t num_channels, tmin, tmax, lags, words, lg;
     double tau0;
     WindowTable tab;
-    const int32_t* pair_lg;    // per pair: log2 of its transform length, or null (all lg)
+    int32_t blocks;            // transforms of sample blocks
     int32_t wrap_lg;           // log2 of the head-tail transform (wrap correction), or -1
 };
 
@@ -1090,8 +987,8 @@ __global__ __launch_bounds__(kThreads) void fft_fixup_kernel(FixArgs a, Weights 
         double acc = 0.0;
         for (int32_t c = 0; c < a.num_channels; ++c) {
             const int64_t sq = b * a.num_channels + c;
-            const int lg = a.pair_lg ? a.pair_lg[sq >> 1] : a.lg;
-            double e = fft_bound(a.fstat, sq, a.seqs, n, lg);
+            double e = a.blocks ? fft_bound_blocks(a.fstat, sq, a.seqs, n)
+                                : fft_bound(a.fstat, sq, a.seqs, n, a.lg);
             if (a.wrap_lg >= 0) e += fft_bound_wrap(a.fstat, sq, a.seqs, a.wrap_lg);
             acc += (double)w.w[c] * e;
         }
@@ -1299,91 +1196,6 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     }
 }
 
-// Length classes of a batch of windows of different lengths (a window table):
-// the class of a pair is the log2 of the smallest power of two (at least 64)
-// holding N + Tmax of each non-empty sequence of the pair, -1 if both are
-// empty.  Writes every pair's class, then the pairs sorted by class (ascending
-// pair index within a class: a stable counting sort in one workgroup) and the
-// start of each class in that list.
-constexpr int kClassThreads = 1024;
-constexpr int kClassWaves = kClassThreads / kWave;
-
-struct ClassArgs {
-    int32_t* pair_lg;          // [pairs]
-    int32_t* list;             // [pairs]
-    int32_t* bounds;           // [kFftClasses + 1]
-    int64_t pairs, seqs, n_all;
-    int32_t num_channels, tmax, lg_max;
-    WindowTable tab;
-};
-
-__device__ int class_of(const ClassArgs& a, int64_t pair) {
-    int lg = -1;
-    for (int64_t s = 2 * pair; s < 2 * pair + 2 && s < a.seqs; ++s) {
-        const int64_t b = s / a.num_channels;
-        const int64_t n = table_n(a.tab, b, a.n_all);
-        if (n <= 0) continue;
-        const int64_t need = n + (int64_t)min(table_tmax(a.tab, b, a.tmax), a.tmax);
-        int l = kFftMinLog2;
-        while (l < a.lg_max && (int64_t(1) << l) < need) ++l;
-        lg = max(lg, l);
-    }
-    return lg;
-}
-
-__global__ __launch_bounds__(kClassThreads) void fft_classify_kernel(ClassArgs a) {
-    __shared__ int32_t run[kFftClasses];
-    __shared__ int32_t wcount[kClassWaves][kFftClasses];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    if (tid < kFftClasses) run[tid] = 0;
-    __syncthreads();
-    for (int64_t p = tid; p < a.pairs; p += kClassThreads) {
-        const int lg = class_of(a, p);
-        a.pair_lg[p] = lg;
-        if (lg >= 0) atomicAdd(&run[lg], 1);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int32_t acc = 0;
-        for (int c = 0; c < kFftClasses; ++c) {
-            const int32_t k = run[c];
-            run[c] = acc;
-            a.bounds[c] = acc;
-            acc += k;
-        }
-        a.bounds[kFftClasses] = acc;
-    }
-    for (int64_t p0 = 0; p0 < a.pairs; p0 += kClassThreads) {
-        for (int i = tid; i < kClassWaves * kFftClasses; i += kClassThreads)
-            wcount[i / kFftClasses][i % kFftClasses] = 0;
-        __syncthreads();
-        const int64_t p = p0 + tid;
-        const int lg = p < a.pairs ? a.pair_lg[p] : -1;   // written by this thread above
-        int rank = 0;
-        uint64_t todo = __ballot(lg >= 0);
-        while (todo) {                                     // one round per class in the wave
-            const int c = __shfl(lg, __builtin_ctzll(todo));
-            const uint64_t same = __ballot(lg == c);
-            if (lg == c) rank = __popcll(same & ((uint64_t(1) << lane) - 1));
-            if (lane == 0) wcount[wave][c] = __popcll(same);
-            todo &= ~same;
-        }
-        __syncthreads();
-        if (lg >= 0) {
-            int32_t off = run[lg] + rank;
-            for (int w = 0; w < wave; ++w) off += wcount[w][lg];
-            a.list[off] = (int32_t)p;
-        }
-        __syncthreads();
-        if (tid < kFftClasses) {
-            int32_t add = 0;
-            for (int w = 0; w < kClassWaves; ++w) add += wcount[w][tid];
-            run[tid] += add;
-        }
-        __syncthreads();
-    }
-}
-
 // Transform geometry of 2^lg points in the launch arguments.
 void set_geometry(FftArgs& a, int lg) {
     int32_t m1, m2, cols;
@@ -1429,10 +1241,7 @@ FftArgs args_of(const Plan& p, const float* x, double* fstat, double* edge, doub
     a.tmax = p.tmax;
     a.lags = p.lags;
     a.tab = p.table;
-    a.list = nullptr;
-    a.bounds = nullptr;
     a.zstride = p.fft_len;
-    a.cls = 0;
     a.seg_start = 0;
     a.seg_len = 0;
     a.wout = nullptr;
@@ -1446,21 +1255,13 @@ FftArgs args_of(const Plan& p, const float* x, double* fstat, double* edge, doub
     return a;
 }
 
-// Workgroups of a ragged launch: the pairs of a class are known only on the
-// GPU, so each launch gets a fixed grid whose workgroups loop over the class.
-constexpr int64_t kRaggedGrid = 4096;
-
-// The transform kernels for the geometry in `a`, over `pairs` pairs (a
-// uniform batch: one workgroup per item), or over at most `pairs` pairs of one
-// length class (ragged: a capped grid).
-template <int kTile, bool kRagged>
+// The transform kernels for the geometry in `a`, over `pairs` pairs.
+template <int kTile>
 void launch_transforms(const FftArgs& a, int64_t pairs, hipStream_t s) {
-    auto grid = [&](int64_t items) {
-        return dim3((unsigned)(kRagged ? std::min(items, kRaggedGrid) : items));
-    };
+    auto grid = [](int64_t items) { return dim3((unsigned)items); };
     if (a.lg2 == 0) {
         const size_t lds = sizeof(double2) * (size_t)a.len;
-        hipLaunchKernelGGL((fft_single_kernel<kTile, kRagged>), grid(pairs), dim3(kTThreads), lds,
+        hipLaunchKernelGGL((fft_single_kernel<kTile>), grid(pairs), dim3(kTThreads), lds,
                            s, a);
         return;
     }
@@ -1474,11 +1275,11 @@ void launch_transforms(const FftArgs& a, int64_t pairs, hipStream_t s) {
     const int64_t rp = int64_t(1) << a.lgr;
     const size_t lds_rows = sizeof(double2) * ((size_t)(2 * rp * m2 + m2 / 2) + fs);
     const int64_t row_groups = pairs * ((m1 / 2 + 1 + rp - 1) / rp);
-    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile, kRagged>), grid(col_groups), dim3(kTThreads),
+    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile>), grid(col_groups), dim3(kTThreads),
                        lds_cols_fwd, s, a);
-    hipLaunchKernelGGL((fft_rows_kernel<kTile, kRagged>), grid(row_groups), dim3(kTThreads),
+    hipLaunchKernelGGL((fft_rows_kernel<kTile>), grid(row_groups), dim3(kTThreads),
                        lds_rows, s, a);
-    hipLaunchKernelGGL((fft_cols_inv_kernel<kTile, kRagged>), grid(col_groups), dim3(kTThreads),
+    hipLaunchKernelGGL((fft_cols_inv_kernel<kTile>), grid(col_groups), dim3(kTThreads),
                        lds_cols, s, a);
 }
 
@@ -1492,19 +1293,10 @@ int64_t twiddle_count_of(int lg) {
 
 }  // namespace
 
-// Complex fp64 entries of the twiddle tables of a plan (a ragged plan: those
-// of every length class, one after another).
+// Complex fp64 entries of the twiddle tables of a plan.
 int64_t fft_twiddle_count(const Plan& p) {
-    if (!p.fft_ragged)
-        return twiddle_count_of(p.fft_log2) + (p.fft_wrap ? twiddle_count_of(p.fft_wrap_log2) : 0);
-    int64_t total = 0;
-    for (int lg = kFftMinLog2; lg <= p.fft_log2; ++lg) total += twiddle_count_of(lg);
-    return total;
-}
-
-// int32 entries of the length-class buffers of a plan.
-int64_t fft_class_ints(const Plan& p) {
-    return p.fft_ragged ? 2 * p.fft_pairs + kFftClasses + 1 : 0;
+    if (p.fft_blocks) return kFftBlockPoints / 2;
+    return twiddle_count_of(p.fft_log2) + (p.fft_wrap ? twiddle_count_of(p.fft_wrap_log2) : 0);
 }
 
 namespace {
@@ -1539,7 +1331,7 @@ void launch_spectrum(const Plan& p, const FftArgs& a, hipStream_t s) {
     const int64_t rp = int64_t(1) << a.lgr;
     const size_t lds_rows = sizeof(double2) * 2 * rp * (size_t)p.fft_m2;
     const int64_t row_groups = p.fft_pairs * ((p.fft_m1 / 2 + 1 + rp - 1) / rp);
-    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile, false>), dim3((unsigned)col_groups),
+    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile>), dim3((unsigned)col_groups),
                        dim3(kTThreads), lds_cols, s, a);
     hipLaunchKernelGGL(spec_rows_kernel<kTile>, dim3((unsigned)row_groups), dim3(kTThreads),
                        lds_rows, s, a);
@@ -1601,11 +1393,11 @@ void launch_wrap(const Plan& p, FftArgs aw, double2* tw, double2* zw, double* wr
     aw.seg_len = p.fft_wrap_m;
     aw.seg_start = 0;                                  // heads
     aw.z = zw;
-    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile, false>), dim3((unsigned)col_groups),
+    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile>), dim3((unsigned)col_groups),
                        dim3(kTThreads), lds_cols_fwd, s, aw);
     aw.seg_start = p.n - p.fft_wrap_m;                 // tails
     aw.z = zw + p.fft_pairs * lw;
-    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile, false>), dim3((unsigned)col_groups),
+    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile>), dim3((unsigned)col_groups),
                        dim3(kTThreads), lds_cols_fwd, s, aw);
     aw.seg_len = 0;
     aw.z = zw;
@@ -1625,14 +1417,14 @@ void launch_wrap(const Plan& p, FftArgs aw, double2* tw, double2* zw, double* wr
                            dim3(kTThreads), lds_rows, s, aw, p.fft_pairs * lw);
     aw.wout = wrap;
     aw.wm = p.fft_wrap_m;
-    hipLaunchKernelGGL((fft_cols_inv_kernel<kTile, false>), dim3((unsigned)col_groups),
+    hipLaunchKernelGGL((fft_cols_inv_kernel<kTile>), dim3((unsigned)col_groups),
                        dim3(kTThreads), lds_cols, s, aw);
 }
 
 }  // namespace
 
 hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, double* edge,
-                             double* tw, double* z, double* part, int32_t* cls, double* zw,
+                             double* tw, double* z, double* part, double* zw,
                              double* wrap, double* s64, float* scores, float w0,
                              hipStream_t s) {
     FftArgs a = args_of(p, x, fstat, edge, tw, z, part);
@@ -1642,63 +1434,39 @@ hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, doubl
         a.scores = scores;
         a.w0 = w0;
     }
-    if (!p.fft_ragged) {
-        launch_twiddles(a, tw2, s);
-        hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)(2 * a.seqs)), dim3(kThreads), 0, s, a);
-        if (p.fft_wrap) {
-            FftArgs aw = a;
-            set_geometry(aw, p.fft_wrap_log2);
-            double2* const tww = tw2 + twiddle_count_of(p.fft_log2);
-            double2* const zw2 = reinterpret_cast<double2*>(zw);
-            if (fft_tile_log2(p.fft_wrap_log2) == kFftSmallTileLog2)
-                launch_wrap<kFftSmallTileLog2>(p, aw, tww, zw2, wrap, s);
-            else
-                launch_wrap<kFftTileLog2>(p, aw, tww, zw2, wrap, s);
-            a.wrap = wrap;
-            a.wrap_w = p.fft_len - p.n;
-            a.wm = p.fft_wrap_m;
-        }
-        if (fft_tile_log2(a.lg) == kFftSmallTileLog2)
-            launch_transforms<kFftSmallTileLog2, false>(a, p.fft_pairs, s);
-        else
-            launch_transforms<kFftTileLog2, false>(a, p.fft_pairs, s);
-        return hipGetLastError();
+    if (p.fft_blocks) {
+        hipLaunchKernelGGL(fft_twiddle_kernel, dim3(kFftBlockPoints / 2 / 256), dim3(256), 0, s,
+                           tw2, kFftBlockLog2, 1, kFftBlockLog2, 0, (int64_t)0, (int64_t)0,
+                           (int64_t)0);
+        hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)a.seqs), dim3(2 * kThreads), 0, s, a);
+        return launch_fft_blocks(p, FftBlockBuffers{tw, z, zw}, x, fstat, edge, part, a.s64,
+                                 a.scores, w0, s);
     }
-    // ragged: classify the pairs, then every length class at its own length
-    ClassArgs ca;
-    ca.pair_lg = cls;
-    ca.list = cls + p.fft_pairs;
-    ca.bounds = cls + 2 * p.fft_pairs;
-    ca.pairs = p.fft_pairs;
-    ca.seqs = a.seqs;
-    ca.n_all = p.n;
-    ca.num_channels = p.num_channels;
-    ca.tmax = p.tmax;
-    ca.lg_max = p.fft_log2;
-    ca.tab = p.table;
-    hipLaunchKernelGGL(fft_classify_kernel, dim3(1), dim3(kClassThreads), 0, s, ca);
-    hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)(2 * a.seqs)), dim3(kThreads), 0, s, a);
-    int64_t tw_off = 0;
-    for (int lg = kFftMinLog2; lg <= p.fft_log2; ++lg) {
-        FftArgs ac = a;
-        set_geometry(ac, lg);
-        ac.tw = tw2 + tw_off;
-        ac.list = ca.list;
-        ac.bounds = ca.bounds;
-        ac.cls = lg;
-        launch_twiddles(ac, tw2 + tw_off, s);
-        if (fft_tile_log2(lg) == kFftSmallTileLog2)
-            launch_transforms<kFftSmallTileLog2, true>(ac, p.fft_pairs, s);
+    launch_twiddles(a, tw2, s);
+    hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)a.seqs), dim3(2 * kThreads), 0, s, a);
+    if (p.fft_wrap) {
+        FftArgs aw = a;
+        set_geometry(aw, p.fft_wrap_log2);
+        double2* const tww = tw2 + twiddle_count_of(p.fft_log2);
+        double2* const zw2 = reinterpret_cast<double2*>(zw);
+        if (fft_tile_log2(p.fft_wrap_log2) == kFftSmallTileLog2)
+            launch_wrap<kFftSmallTileLog2>(p, aw, tww, zw2, wrap, s);
         else
-            launch_transforms<kFftTileLog2, true>(ac, p.fft_pairs, s);
-        tw_off += twiddle_count_of(lg);
+            launch_wrap<kFftTileLog2>(p, aw, tww, zw2, wrap, s);
+        a.wrap = wrap;
+        a.wrap_w = p.fft_len - p.n;
+        a.wm = p.fft_wrap_m;
     }
+    if (fft_tile_log2(a.lg) == kFftSmallTileLog2)
+        launch_transforms<kFftSmallTileLog2>(a, p.fft_pairs, s);
+    else
+        launch_transforms<kFftTileLog2>(a, p.fft_pairs, s);
     return hipGetLastError();
 }
 
 hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                            const int32_t* cls, double* s64, float* scores,
-                            const SelectBuffers& sb, hipStream_t s) {
+                            double* s64, float* scores, const SelectBuffers& sb,
+                            hipStream_t s) {
     FixArgs a;
     a.x = x;
     a.fstat = fstat;
@@ -1718,7 +1486,7 @@ hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, con
     a.lg = p.fft_log2;
     a.tau0 = kFftRelBound;
     a.tab = p.table;
-    a.pair_lg = p.fft_ragged ? cls : nullptr;
+    a.blocks = p.fft_blocks;
     a.wrap_lg = p.fft_wrap ? p.fft_wrap_log2 : -1;
     hipLaunchKernelGGL(fft_fixup_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s, a,
                        w);

@@ -43,7 +43,11 @@ constexpr int kFftMinLog2 = 6;
 // holds four rows of up to 2^10 points in one 2^12-point tile).
 constexpr int kFftWrapMinLog2 = 12;
 constexpr int kFftWrapMaxLog2 = 20;
-constexpr int kFftClasses = kFftMaxLog2 + 1;   // length classes 2^lg of a ragged batch, by lg
+// FFT scores from transforms of sample blocks (fft_blocks.hip): points a
+// transform and samples a block.
+constexpr int kFftBlockLog2 = 12;
+constexpr int kFftBlockPoints = 1 << kFftBlockLog2;
+constexpr int kFftBlockSamples = kFftBlockPoints / 2;
 // Matrix-core scores (GPOEO_PD_MFMA_SCORES): lags per wavefront tile, zero
 // padding before and after each digit plane (bytes; the LDS staging reads
 // 16-byte chunks that start before N, so at most 15 bytes past N, and A rows
@@ -155,12 +159,8 @@ struct Plan {
     // and imaginary parts of one complex transform.  Up to 2^12 points one
     // workgroup transforms a pair in LDS; beyond that the transform is split
     // as fft_len = fft_m1 * fft_m2 (columns of fft_m1 points, rows of fft_m2).
-    // A ragged FFT plan (windows from a table, of different lengths) gives
-    // each pair the shortest transform its two sequences need: the pairs are
-    // sorted into length classes 2^lg, lg in [kFftMinLog2, fft_log2], on the
-    // GPU, and every class runs at its own length.
     bool fft;
-    bool fft_ragged;
+    bool fft_table;          // windows from a table (always by sample blocks)
     int32_t fft_log2, fft_m1, fft_m2, fft_cols;
     int64_t fft_len;
     int64_t fft_pairs;
@@ -171,6 +171,11 @@ struct Plan {
     // 2^fft_wrap_log2 >= 2M points per pair computes it, and it is subtracted.
     bool fft_wrap;
     int32_t fft_wrap_m, fft_wrap_log2;
+    // Scores from transforms of sample blocks: blk_nb blocks and blk_j lag
+    // tiles of the longest window, blk_pairs pairs a launch.
+    bool fft_blocks;
+    int32_t blk_nb, blk_j;
+    int64_t blk_pairs;
     // Matrix-core scores: every sequence as four int8 digit planes of
     // mfma_plane bytes (padded); lag tiles of kMfmaTileLags from mfma_t0
     // (Tmin).
@@ -193,7 +198,7 @@ struct Plan {
     int32_t bitmap_words;    // 32-bit words per window of the exactness bitmap
     // workspace layout (byte offsets, 256-byte aligned)
     size_t off_var, off_s64, off_bits, off_state, off_queue, off_part, off_cut;
-    size_t off_fstat, off_edge, off_tw, off_z, off_cls, off_zw, off_wrap, off_dig, off_qstat,
+    size_t off_fstat, off_edge, off_tw, off_z, off_zw, off_wrap, off_dig, off_qstat,
         off_rpart, bytes;
 };
 
@@ -237,6 +242,14 @@ struct RollingCombineArgs {
     double diff_threshold;
 };
 
+// For gpoeo_pd_detect_noalloc: the smallest workspace a call can run in, and the
+// call in a workspace of at least that (an FFT plan whose sample blocks need
+// more takes the long transforms).
+int least_workspace(const gpoeo_pd_desc* desc, size_t* bytes);
+int detect_within(const gpoeo_pd_desc* desc, const float* x, float* scores,
+                  gpoeo_pd_result* results, void* workspace, size_t workspace_bytes,
+                  hipStream_t stream);
+
 // Kernel launchers; each returns hipGetLastError() after enqueueing.
 // var: [B][C][2] = population variance, mean |x| per window and channel.
 // fstat (nullable): [B*C][4] = mean, sum (x - mean)^2, sum |x - mean|, 0.
@@ -252,31 +265,37 @@ hipError_t launch_finalize_blocks(const Plan& p, const Weights& w, const double*
 hipError_t launch_finalize(const Plan& p, const Weights& w, const double* part, double* s64,
                            float* scores, hipStream_t s);
 // FFT scores.  fstat: [B*C][4] = mean, sum of squares and sum of |.| of the
-// centred sequence, and its absolute error bound on D(T); edge: [B*C][2][Tmax+1]
-// prefix sums of squares from the head and from the tail; tw: twiddle tables;
+// centred sequence, and its absolute error bound on D(T); edge: [B*C][Tmax+1]
+// energies of the first and last N - T samples together; tw: twiddle tables;
 // z: [pairs][fft_len] complex fp64.  Writes D_c(T) into part ([B*C][lags]).
-// cls (ragged plans): [pairs] class of each pair, [pairs] pairs sorted by class,
-// [kFftClasses + 1] start of each class; null otherwise.
 int64_t fft_twiddle_count(const Plan& p);
-int64_t fft_class_ints(const Plan& p);
 // zw, wrap (wrap-corrected plans): [2][pairs][2^fft_wrap_log2] complex fp64
 // head and tail transforms; [B*C][M] fp64 wrap terms.  Null otherwise.
 // With one channel the transforms also do the finalisation: s64 and scores
 // (nullable) receive S(T) = w_0 D(T) / (N - T) directly and `part` is not
-// written.  Not for a window table (ragged plans) with fp32 scores requested:
+// written.  Not for a window table with fp32 scores requested:
 // lags past a short window's transform are then zeroed by the finalisation.
 inline bool fft_fused_finalize(const Plan& p, bool with_scores) {
-    return p.fft && p.num_channels == 1 && (!p.fft_ragged || !with_scores);
+    return p.fft && p.num_channels == 1 && (!p.fft_table || !with_scores);
 }
+// Sample blocks (p.fft_blocks): twiddles [kFftBlockPoints / 2], spectra
+// [2 blk_pairs][blk_nb][kFftBlockSamples] and lag-tile spectra
+// [2 blk_pairs][blk_j][kFftBlockSamples], complex fp64.
+struct FftBlockBuffers {
+    double *tw, *z, *r;
+};
+hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const float* x,
+                             const double* fstat, double* edge, double* part, double* s64,
+                             float* scores, float w0, hipStream_t s);
 hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, double* edge,
-                             double* tw, double* z, double* part, int32_t* cls, double* zw,
+                             double* tw, double* z, double* part, double* zw,
                              double* wrap, double* s64, float* scores, float w0,
                              hipStream_t s);
 // After the finalisation: every lag whose FFT bound does not give the tier-0
 // guarantee is re-scored in fp64 (score, fp32 score and tier-1 bit).
 hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                            const int32_t* cls, double* s64, float* scores,
-                            const SelectBuffers& sb, hipStream_t s);
+                            double* s64, float* scores, const SelectBuffers& sb,
+                            hipStream_t s);
 
 // Matrix-core scores: per sequence the centre, scale and exactness (qstat
 // [S][4]), the digit planes, the edge sums and D(T) into `part`, or with one

@@ -58,12 +58,12 @@ int scratch_on_current_device(hipStream_t stream, void** out) {
 extern "C" int gpoeo_pd_detect_noalloc(const gpoeo_pd_desc* desc, const float* x, float* scores,
                                        gpoeo_pd_result* results, hipStream_t stream) {
     size_t need = 0;
-    const int rc = gpoeo_pd_workspace_bytes(desc, &need);   // validates desc (host only)
+    const int rc = gpoeo::least_workspace(desc, &need);   // validates desc (host only)
     if (rc != GPOEO_PD_OK) return rc;
     if (!x || (!results && !(desc->flags & GPOEO_PD_SCORES_ONLY))) return GPOEO_PD_EINVAL;
     if (need > kScratchBytes) return GPOEO_PD_ETOOBIG;
     void* ws = nullptr;
     const int sc = scratch_on_current_device(stream, &ws);
     if (sc != GPOEO_PD_OK) return sc;
-    return gpoeo_pd_detect(desc, x, scores, results, ws, kScratchBytes, stream);
+    return gpoeo::detect_within(desc, x, scores, results, ws, kScratchBytes, stream);
 }
