@@ -859,7 +859,7 @@ namespace {
 // transforms, amplitudes).
 struct SpectralPlan {
     gpoeo::Plan p;
-    size_t off_var, off_fstat, off_tw, off_z, off_amp, bytes;
+    size_t off_var, off_fstat, off_tw, off_z, off_amp, off_chunk, bytes;
 };
 
 int make_spectral(const gpoeo_pd_desc* d, const gpoeo_pd_spectral_params* sp, SpectralPlan* r) {
@@ -882,6 +882,9 @@ int make_spectral(const gpoeo_pd_desc* d, const gpoeo_pd_spectral_params* sp, Sp
     if (!gpoeo::mul_ok(r->p.fft_pairs, r->p.fft_len, &n_z) || n_z > (INT64_MAX / 64) ||
         !gpoeo::mul_ok(seqs, r->p.fft_len / 2 + 1, &n_amp) || n_amp > (INT64_MAX / 16))
         return GPOEO_PD_EINVAL;
+    // one workgroup per chunk of a window's spectrum
+    if (d->num_windows > ((int64_t(1) << 32) - 1) / 256 / gpoeo::spectral_chunks(r->p))
+        return GPOEO_PD_EINVAL;
     if (r->p.fft_m2 == 1) n_z = 0;                 // one workgroup per pair: no transform buffer
     size_t off = 0;
     r->off_var = off;
@@ -894,6 +897,8 @@ int make_spectral(const gpoeo_pd_desc* d, const gpoeo_pd_spectral_params* sp, Sp
     off = gpoeo::align_up(off + (size_t)n_z * 2 * sizeof(double));
     r->off_amp = off;
     off = gpoeo::align_up(off + (size_t)n_amp * sizeof(double));
+    r->off_chunk = off;
+    off = gpoeo::align_up(off + gpoeo::spectral_chunk_bytes(r->p));
     r->bytes = off;
     return GPOEO_PD_OK;
 }
@@ -929,7 +934,8 @@ int gpoeo_pd_spectral_candidates(const gpoeo_pd_desc* desc, const gpoeo_pd_spect
     if (gpoeo::launch_window_stats(r.p, x, var, fstat, stream) != hipSuccess) return GPOEO_PD_EHIP;
     if (gpoeo::launch_spectral(r.p, w, x, fstat, reinterpret_cast<double*>(ws + r.off_tw),
                                reinterpret_cast<double*>(ws + r.off_z),
-                               reinterpret_cast<double*>(ws + r.off_amp), params->c_peak,
+                               reinterpret_cast<double*>(ws + r.off_amp), ws + r.off_chunk,
+                               params->c_peak,
                                params->max_candidates, results, stream) != hipSuccess)
         return GPOEO_PD_EHIP;
     return GPOEO_PD_OK;

@@ -1038,26 +1038,103 @@ __global__ __launch_bounds__(kThreads) void fft_fixup_kernel(FixArgs a, Weights 
     }
 }
 
+// What a chunk of kSpecChunk bins of one window's spectrum holds.
+struct SpecChunk {
+    double top;                // largest peak (0: none)
+    double most;               // largest amplitude
+    int64_t peaks;
+};
+
 struct SpecSelArgs {
-    double* amp;               // [S][half]: per-channel amplitudes, channel 0 overwritten by A
+    const double* amp;         // [S][half]: per-channel amplitudes
     const double* fstat;       // [S][4]
+    SpecChunk* chunk;          // [B][chunks]
     gpoeo_pd_spectral_result* out;
     int64_t seqs, half, len;
-    int32_t num_channels, tmin, tmax, k_max, lg;
+    int32_t num_channels, tmin, tmax, k_max, lg, chunks;
     double c_peak;
 };
 
 constexpr int kCandCap = 1024;   // candidates collected per window
+constexpr int kSpecChunk = kSpecChunkBins;
 
-// Candidates of one window from its amplitude spectrum A(k) = sum_c w_c |X_c(k)|:
-// peaks (2 <= k <= L/2 - 1, A(k) > A(k-1), A(k) >= A(k+1)), the largest peak,
-// then the peaks above c_peak times it whose period round(L/k) is in
-// [tmin, tmax], strongest first (ties: smaller k).  The window is flagged
+// A(k) = sum_c w_c |X_c(k)| of window b, in channel order.
+__device__ __forceinline__ double spec_amp(const SpecSelArgs& a, const Weights& w, int64_t b,
+                                           int64_t k) {
+    const double* __restrict__ amp = a.amp + b * a.num_channels * a.half + k;
+    double acc = 0.0;
+    for (int32_t c = 0; c < a.num_channels; ++c) acc += (double)w.w[c] * amp[c * a.half];
+    return acc;
+}
+
+// Peaks of one chunk of one window's spectrum (2 <= k <= L/2 - 1, A(k) > A(k-1),
+// A(k) >= A(k+1)): their number, the largest, and the largest amplitude.  A
+// workgroup per chunk, so that few windows of long spectra fill the chip: the
+// selection of 300 windows of 131,073 bins and two channels took 462 us with
+// one workgroup a window, which wrote the channel sums back and read them twice.
+__global__ __launch_bounds__(kThreads) void spec_scan_kernel(SpecSelArgs a, Weights w) {
+    constexpr int kPer = kSpecChunk / kThreads;
+    __shared__ double s[kSpecChunk + 2];
+    __shared__ double red[2][kThreads / kWave];
+    __shared__ int32_t redi[kThreads / kWave];
+    const int64_t b = blockIdx.x / a.chunks;
+    const int32_t ch = (int32_t)(blockIdx.x % a.chunks);
+    const int64_t k0 = (int64_t)ch * kSpecChunk;         // bins k0 .. k0 + kSpecChunk - 1
+    const int tid = threadIdx.x;
+    double v[kPer], e = 0.0;                             // all loads in flight
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int64_t k = k0 + tid + r * kThreads;
+        v[r] = k < a.half ? spec_amp(a, w, b, k) : 0.0;
+    }
+    const int64_t ke = tid == 0 ? k0 - 1 : k0 + kSpecChunk;   // the neighbours
+    if (tid < 2 && ke >= 0 && ke < a.half) e = spec_amp(a, w, b, ke);
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) s[1 + tid + r * kThreads] = v[r];
+    if (tid < 2) s[tid == 0 ? 0 : kSpecChunk + 1] = e;
+    __syncthreads();
+    double top = 0.0, most = 0.0;
+    int32_t peaks = 0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int i = 1 + tid + r * kThreads;
+        const int64_t k = k0 + i - 1;
+        most = fmax(most, v[r]);
+        if (k >= 2 && k <= a.half - 2 && v[r] > s[i - 1] && v[r] >= s[i + 1]) {
+            ++peaks;
+            top = fmax(top, v[r]);
+        }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        top = fmax(top, __shfl_xor(top, o));
+        most = fmax(most, __shfl_xor(most, o));
+        peaks += __shfl_xor(peaks, o);
+    }
+    if ((tid & (kWave - 1)) == 0) {
+        red[0][tid / kWave] = top;
+        red[1][tid / kWave] = most;
+        redi[tid / kWave] = peaks;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        SpecChunk c = {top, most, peaks};
+        for (int i = 1; i < kThreads / kWave; ++i) {
+            c.top = fmax(c.top, red[0][i]);
+            c.most = fmax(c.most, red[1][i]);
+            c.peaks += redi[i];
+        }
+        a.chunk[blockIdx.x] = c;
+    }
+}
+
+// Candidates of one window from its amplitude spectrum: the peaks above c_peak
+// times the largest one whose period round(L/k) is in [tmin, tmax], strongest
+// first (ties: smaller k).  Only chunks whose largest amplitude reaches that
+// threshold (within the error bound) are read again.  The window is flagged
 // UNRESOLVED when a peak test, the threshold, or the order of the reported
 // candidates lies within four times the amplitude error bound (the list a
 // correctly rounded spectrum gives could then differ), or when more than
 // kCandCap candidates qualify.
-template <int kThreads>
 __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, Weights w) {
     __shared__ double red[kThreads];
     __shared__ int32_t redi[kThreads];
@@ -1065,30 +1142,21 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     __shared__ int32_t cand_k[kCandCap];
     __shared__ int32_t ncand;
     __shared__ int32_t flag;
+    __shared__ gpoeo_pd_spectral_result res;
     const int64_t b = blockIdx.x;
     const int tid = threadIdx.x;
-    const int64_t half = a.half;               // L/2 + 1 bins
-    double* __restrict__ amp = a.amp + b * a.num_channels * half;
-    // 1. channel sum in channel order (into channel 0)
-    for (int64_t k = tid; k < half; k += kThreads) {
-        double acc = 0.0;
-        for (int32_t c = 0; c < a.num_channels; ++c) acc += (double)w.w[c] * amp[c * half + k];
-        amp[k] = acc;
-    }
+    const SpecChunk* __restrict__ chunk = a.chunk + b * a.chunks;
     if (tid == 0) {
         ncand = 0;
         flag = 0;
     }
-    __syncthreads();
-    // 2. peaks and the largest one
+    for (int i = tid; i < (int)(sizeof(res) / 4); i += kThreads) reinterpret_cast<int32_t*>(&res)[i] = 0;
+    // 1. the largest peak and the number of peaks
     double mx = 0.0;
     int32_t npk = 0;
-    for (int64_t k = 2 + tid; k <= half - 2; k += kThreads) {
-        const double v = amp[k];
-        if (v > amp[k - 1] && v >= amp[k + 1]) {
-            ++npk;
-            mx = fmax(mx, v);
-        }
+    for (int32_t i = tid; i < a.chunks; i += kThreads) {
+        mx = fmax(mx, chunk[i].top);
+        npk += (int32_t)chunk[i].peaks;
     }
     red[tid] = mx;
     redi[tid] = npk;
@@ -1103,7 +1171,7 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     const double top = red[0];
     const int32_t n_peaks = redi[0];
     __syncthreads();
-    // 3. error bound of A (any k): the transform bound of each channel's pair
+    // 2. error bound of A (any k): the transform bound of each channel's pair
     // (as for the FFT scores: phi sqrt(L) zeta, plus the separation), summed
     // with the weights, plus the rounding of the amplitude and the channel sum
     const double u = 1.1102230246251565e-16;
@@ -1120,30 +1188,34 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     eps = 2.0 * (eps + ((double)a.num_channels + 6.0) * u * top);
     const double m = 4.0 * eps;
     const double thr = a.c_peak * top;
-    // 4. candidates, and decisions too close to call
-    for (int64_t k = 2 + tid; k <= half - 2; k += kThreads) {
-        const double v = amp[k];
-        if (v + m < a.c_peak * (top - m)) continue;       // cannot matter
-        const double l = amp[k - 1], r = amp[k + 1];
-        const bool peak = v > l && v >= r;
-        if (fabs(v - l) <= m || fabs(v - r) <= m) atomicOr(&flag, 1);
-        if (!peak) continue;
-        const int64_t t = (2 * a.len + k) / (2 * k);       // round(L / k), halves up
-        if (t < a.tmin || t > a.tmax) continue;
-        if (fabs(v - thr) <= m * (1.0 + a.c_peak)) atomicOr(&flag, 1);
-        if (!(v > thr)) continue;
-        const int slot = atomicAdd(&ncand, 1);
-        if (slot < kCandCap) {
-            cand_a[slot] = v;
-            cand_k[slot] = (int32_t)k;
-        } else {
-            atomicOr(&flag, 2);
+    // 3. candidates, and decisions too close to call
+    for (int32_t i = 0; i < a.chunks; ++i) {
+        if (chunk[i].most + m < a.c_peak * (top - m)) continue;   // the same for every thread
+        const int64_t k0 = (int64_t)i * kSpecChunk;
+        const int64_t k1 = min(k0 + (int64_t)kSpecChunk - 1, a.half - 2);
+        for (int64_t k = max(k0, (int64_t)2) + tid; k <= k1; k += kThreads) {
+            const double v = spec_amp(a, w, b, k);
+            if (v + m < a.c_peak * (top - m)) continue;       // cannot matter
+            const double l = spec_amp(a, w, b, k - 1), r = spec_amp(a, w, b, k + 1);
+            const bool peak = v > l && v >= r;
+            if (fabs(v - l) <= m || fabs(v - r) <= m) atomicOr(&flag, 1);
+            if (!peak) continue;
+            const int64_t t = (2 * a.len + k) / (2 * k);       // round(L / k), halves up
+            if (t < a.tmin || t > a.tmax) continue;
+            if (fabs(v - thr) <= m * (1.0 + a.c_peak)) atomicOr(&flag, 1);
+            if (!(v > thr)) continue;
+            const int slot = atomicAdd(&ncand, 1);
+            if (slot < kCandCap) {
+                cand_a[slot] = v;
+                cand_k[slot] = (int32_t)k;
+            } else {
+                atomicOr(&flag, 2);
+            }
         }
     }
     __syncthreads();
     const int nc = min(ncand, kCandCap);
-    // 5. the strongest first: rounds of a block-wide arg-max (larger A, then smaller k)
-    gpoeo_pd_spectral_result res = {};
+    // 4. the strongest first: rounds of a block-wide arg-max (larger A, then smaller k)
     double prev = 0.0;
     int rounds = min(nc, a.k_max + 1);                     // one more to check the order
     for (int r = 0; r < rounds; ++r) {
@@ -1157,22 +1229,30 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
                 bi = i;
             }
         }
-        red[tid] = bv;
-        redi[tid] = bi;
-        __syncthreads();
-        for (int st = kThreads / 2; st > 0; st >>= 1) {
-            if (tid < st) {
-                const int i1 = redi[tid + st], i0 = redi[tid];
-                const double v1 = red[tid + st], v0 = red[tid];
-                if (i1 >= 0 && (i0 < 0 || v1 > v0 || (v1 == v0 && cand_k[i1] < cand_k[i0]))) {
-                    red[tid] = v1;
-                    redi[tid] = i1;
-                }
+        // wavefront arg-max, then the four wavefronts' in order
+        for (int o = kWave / 2; o > 0; o >>= 1) {
+            const double v1 = __shfl_xor(bv, o);
+            const int32_t k1 = __shfl_xor(bk, o), i1 = __shfl_xor(bi, o);
+            if (i1 >= 0 && (bi < 0 || v1 > bv || (v1 == bv && k1 < bk))) {
+                bv = v1;
+                bk = k1;
+                bi = i1;
             }
-            __syncthreads();
         }
-        const int best = redi[0];
-        const double bvv = red[0];
+        if ((tid & (kWave - 1)) == 0) {
+            red[tid / kWave] = bv;
+            redi[tid / kWave] = bi;
+        }
+        __syncthreads();
+        int best = redi[0];
+        double bvv = red[0];
+        for (int i = 1; i < kThreads / kWave; ++i) {
+            const int i1 = redi[i];
+            if (i1 >= 0 && (best < 0 || red[i] > bvv || (red[i] == bvv && cand_k[i1] < cand_k[best]))) {
+                best = i1;
+                bvv = red[i];
+            }
+        }
         __syncthreads();
         if (tid == 0) {
             if (r > 0 && prev - bvv <= m) flag |= 1;
@@ -1192,8 +1272,10 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
         res.n_peaks = n_peaks;
         res.max_peak = top;
         res.flags = flag ? GPOEO_PD_UNRESOLVED : 0u;
-        a.out[b] = res;
     }
+    __syncthreads();
+    int32_t* out = reinterpret_cast<int32_t*>(a.out + b);
+    for (int i = tid; i < (int)(sizeof(res) / 4); i += kThreads) out[i] = reinterpret_cast<int32_t*>(&res)[i];
 }
 
 // Transform geometry of 2^lg points in the launch arguments.
@@ -1339,9 +1421,14 @@ void launch_spectrum(const Plan& p, const FftArgs& a, hipStream_t s) {
 
 }  // namespace
 
+int64_t spectral_chunks(const Plan& p) { return (p.fft_len / 2 + kSpecChunk) / kSpecChunk; }
+size_t spectral_chunk_bytes(const Plan& p) {
+    return (size_t)(p.num_windows * spectral_chunks(p)) * sizeof(SpecChunk);
+}
+
 hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                           double* tw, double* z, double* amp, double c_peak, int32_t k_max,
-                           gpoeo_pd_spectral_result* out, hipStream_t s) {
+                           double* tw, double* z, double* amp, void* chunk, double c_peak,
+                           int32_t k_max, gpoeo_pd_spectral_result* out, hipStream_t s) {
     FftArgs a = args_of(p, x, const_cast<double*>(fstat), nullptr, tw, z, nullptr);
     a.amp = amp;
     launch_twiddles(a, reinterpret_cast<double2*>(tw), s);
@@ -1362,12 +1449,12 @@ hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, cons
     sa.k_max = k_max;
     sa.lg = p.fft_log2;
     sa.c_peak = c_peak;
-    if (sa.half > 16384)   // long spectra: more of each window's bins in flight
-        hipLaunchKernelGGL(spec_select_kernel<1024>, dim3((unsigned)p.num_windows), dim3(1024), 0,
-                           s, sa, w);
-    else
-        hipLaunchKernelGGL(spec_select_kernel<kThreads>, dim3((unsigned)p.num_windows),
-                           dim3(kThreads), 0, s, sa, w);
+    sa.chunk = static_cast<SpecChunk*>(chunk);
+    sa.chunks = (int32_t)spectral_chunks(p);
+    hipLaunchKernelGGL(spec_scan_kernel, dim3((unsigned)(p.num_windows * sa.chunks)),
+                       dim3(kThreads), 0, s, sa, w);
+    hipLaunchKernelGGL(spec_select_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s,
+                       sa, w);
     return hipGetLastError();
 }
 

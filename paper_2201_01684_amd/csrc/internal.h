@@ -63,6 +63,7 @@ constexpr int kMfmaFlush = 512;
 // partial cross terms a combination kernel adds in chunk order.
 constexpr int kMfmaTargetWaves = 4096;
 constexpr int kMfmaMinChunkSteps = 64;
+constexpr int kSpecChunkBins = 2048;   // bins a workgroup of the spectral scan takes
 inline int fft_tile_log2(int lg) { return lg <= 2 * (kFftSmallTileLog2 - 1) ? kFftSmallTileLog2 : kFftTileLog2; }
 
 struct Weights {
@@ -314,10 +315,13 @@ hipError_t launch_mfma_fixup(const Plan& p, const Weights& w, const float* x,
                              const SelectBuffers& sb, hipStream_t s);
 hipError_t launch_select_init(const Plan& p, const SelectBuffers& sb, hipStream_t s);
 // Spectral candidates (Algorithm 1's FFT front end) of every window: a plan
-// whose FFT geometry is that of L = 2^k >= N; amp: [B*C][L/2 + 1] fp64.
+// whose FFT geometry is that of L = 2^k >= N; amp: [B*C][L/2 + 1] fp64; chunk:
+// spectral_chunk_bytes (the scan of spectral_chunks chunks of bins a window).
+int64_t spectral_chunks(const Plan& p);
+size_t spectral_chunk_bytes(const Plan& p);
 hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                           double* tw, double* z, double* amp, double c_peak, int32_t k_max,
-                           gpoeo_pd_spectral_result* out, hipStream_t s);
+                           double* tw, double* z, double* amp, void* chunk, double c_peak,
+                           int32_t k_max, gpoeo_pd_spectral_result* out, hipStream_t s);
 // Transform of 2^lg points: one workgroup (m2 = 1), or m1 columns of m2 rows
 // with `cols` columns per column workgroup.
 void fft_geometry(int32_t lg, int32_t* m1, int32_t* m2, int32_t* cols);
