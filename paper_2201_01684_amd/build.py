@@ -23,7 +23,7 @@ OBJ_DIR = os.path.join(ROOT, "_build", "obj")
 LIB_NAME = "libgpoeo_pd.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 
-SOURCES = ["api.cpp", "lag_score.hip", "window_stats.hip", "select.hip", "rolling.hip",
+SOURCES = ["api.cpp", "lag_score.hip", "lag_score_tiny.hip", "window_stats.hip", "select.hip", "rolling.hip",
            "similarity.hip", "fft_score.hip", "fft_blocks.hip", "centred.hip", "mfma_score.hip", "noalloc.hip"]
 # The selection re-evaluates scores and thresholds as plain fp64 expressions
 # (one rounding per operation, as written); no multiply-add contraction there,
@@ -32,6 +32,7 @@ SOURCES = ["api.cpp", "lag_score.hip", "window_stats.hip", "select.hip", "rollin
 # bit for bit.
 EXTRA_FLAGS = {"select.hip": ["-ffp-contract=off"], "rolling.hip": ["-ffp-contract=off"],
                "window_stats.hip": ["-ffp-contract=off"],
+               "lag_score_tiny.hip": ["-ffp-contract=off"],
                "similarity.hip": ["-ffp-contract=off"], "fft_score.hip": ["-ffp-contract=off"],
                "fft_blocks.hip": ["-ffp-contract=off"],
                "centred.hip": ["-ffp-contract=off"], "mfma_score.hip": ["-ffp-contract=off"]}

@@ -469,7 +469,7 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
     double* fstat = p.fft ? reinterpret_cast<double*>(static_cast<char*>(workspace) + p.off_fstat)
                           : nullptr;
     if ((!scores_only || p.fft) && !p.fused &&
-        gpoeo::launch_window_stats(p, x, c.var, fstat, stream) != hipSuccess)
+        gpoeo::launch_window_stats(p, x, c.var, fstat, &c.sb, stream) != hipSuccess)
         return GPOEO_PD_EHIP;
     if (!mark(1)) return GPOEO_PD_EHIP;
     if (p.fft) {
@@ -485,7 +485,6 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
         if (!mark(2)) return GPOEO_PD_EHIP;
         if ((!gpoeo::fft_fused_finalize(p, scores != nullptr) &&
              gpoeo::launch_finalize(p, w, c.part, c.s64, scores, stream) != hipSuccess) ||
-            gpoeo::launch_select_init(p, c.sb, stream) != hipSuccess ||
             gpoeo::launch_fft_fixup(p, w, x, fstat, c.s64, scores, c.sb, stream) !=
                 hipSuccess)
             return GPOEO_PD_EHIP;
@@ -500,7 +499,7 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
         if (!mark(2)) return GPOEO_PD_EHIP;
         if ((!gpoeo::mfma_fused_finalize(p, scores != nullptr) &&
              gpoeo::launch_finalize(p, w, c.part, c.s64, scores, stream) != hipSuccess) ||
-            gpoeo::launch_select_init(p, c.sb, stream) != hipSuccess ||
+            (scores_only && gpoeo::launch_select_init(p, c.sb, stream) != hipSuccess) ||
             gpoeo::launch_mfma_fixup(p, w, x, qstat, c.s64, scores, c.sb, stream) != hipSuccess)
             return GPOEO_PD_EHIP;
     } else if (p.sliding) {
@@ -510,9 +509,11 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
         if (gpoeo::launch_finalize_blocks(p, w, c.part, c.cut, c.s64, scores, stream) != hipSuccess)
             return GPOEO_PD_EHIP;
     } else if (p.fused) {
-        // statistics, finalisation and selection all run in the finish kernel
-        // (timed as the finalisation stage; the other two stages are empty)
-        if (gpoeo::launch_lag_score(p, x, c.part, stream) != hipSuccess) return GPOEO_PD_EHIP;
+        // statistics (of tiny plans beside the scores), finalisation and selection
+        // all run in the finish kernel (timed as the finalisation stage; the
+        // other two stages are empty)
+        if (gpoeo::launch_lag_score(p, x, c.part, p.tiny && !scores_only ? c.var : nullptr,
+                                    stream) != hipSuccess) return GPOEO_PD_EHIP;
         if (!mark(2)) return GPOEO_PD_EHIP;
         if (gpoeo::launch_finish(p, w, x, c.var, c.part, c.s64, scores, c.sb, results, stream) !=
             hipSuccess)
@@ -520,15 +521,13 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
         if (!mark(3) || !mark(4)) return GPOEO_PD_EHIP;
         return GPOEO_PD_OK;
     } else {
-        if (gpoeo::launch_lag_score(p, x, c.part, stream) != hipSuccess) return GPOEO_PD_EHIP;
+        if (gpoeo::launch_lag_score(p, x, c.part, nullptr, stream) != hipSuccess) return GPOEO_PD_EHIP;
         if (!mark(2)) return GPOEO_PD_EHIP;
         if (gpoeo::launch_finalize(p, w, c.part, c.s64, scores, stream) != hipSuccess)
             return GPOEO_PD_EHIP;
     }
     if (!mark(3)) return GPOEO_PD_EHIP;
     if (!scores_only) {
-        if (!p.fft && !p.mfma && gpoeo::launch_select_init(p, c.sb, stream) != hipSuccess)
-            return GPOEO_PD_EHIP;
         if (gpoeo::launch_select(p, w, x, c.var, c.s64, c.sb, results, stream) != hipSuccess)
             return GPOEO_PD_EHIP;
     }
@@ -931,7 +930,7 @@ int gpoeo_pd_spectral_candidates(const gpoeo_pd_desc* desc, const gpoeo_pd_spect
     double* var = reinterpret_cast<double*>(ws + r.off_var);
     double* fstat = reinterpret_cast<double*>(ws + r.off_fstat);
     const gpoeo::Weights w = weights_of(desc, r.p.num_channels);
-    if (gpoeo::launch_window_stats(r.p, x, var, fstat, stream) != hipSuccess) return GPOEO_PD_EHIP;
+    if (gpoeo::launch_window_stats(r.p, x, var, fstat, nullptr, stream) != hipSuccess) return GPOEO_PD_EHIP;
     if (gpoeo::launch_spectral(r.p, w, x, fstat, reinterpret_cast<double*>(ws + r.off_tw),
                                reinterpret_cast<double*>(ws + r.off_z),
                                reinterpret_cast<double*>(ws + r.off_amp), ws + r.off_chunk,

@@ -17,7 +17,7 @@ namespace exact {
 // the next chunk are issued before the additions of the current one.
 constexpr int kChunk = 32;
 
-template <typename F>
+template <int kChunk, typename F>
 __device__ __forceinline__ void for_pairs(const float* __restrict__ a, const float* __restrict__ b,
                                           int64_t m, F&& step) {
     float ca[kChunk], cb[kChunk], na[kChunk], nb[kChunk];
@@ -53,6 +53,7 @@ __device__ __forceinline__ void for_pairs(const float* __restrict__ a, const flo
 }
 
 // Plain sequential fp64 evaluation of S(T) = sum_c w_c * D_c(T) / (N - T).
+template <int kC = kChunk>
 __device__ inline double exact_score(const float* __restrict__ xw, int32_t num_channels,
                               int64_t channel_stride, int64_t n, int64_t t, const Weights& w) {
 #pragma clang fp contract(off)
@@ -61,7 +62,7 @@ __device__ inline double exact_score(const float* __restrict__ xw, int32_t num_c
         const float* __restrict__ xc = xw + (int64_t)c * channel_stride;
         const int64_t m = n - t;
         double dsum = 0.0;
-        for_pairs(xc, xc + t, m, [&](float u, float v) {
+        for_pairs<kC>(xc, xc + t, m, [&](float u, float v) {
 #pragma clang fp contract(off)
             const double d = (double)u - (double)v;
             dsum = dsum + d * d;
@@ -72,6 +73,7 @@ __device__ inline double exact_score(const float* __restrict__ xw, int32_t num_c
 }
 
 // Plain sequential fp64 evaluation of R = 2 * sum_c w_c * Var_c (two passes).
+template <int kC = kChunk>
 __device__ inline double exact_reference(const float* __restrict__ xw, int32_t num_channels,
                                   int64_t channel_stride, int64_t n, const Weights& w) {
 #pragma clang fp contract(off)
@@ -79,10 +81,10 @@ __device__ inline double exact_reference(const float* __restrict__ xw, int32_t n
     for (int32_t c = 0; c < num_channels; ++c) {
         const float* __restrict__ xc = xw + (int64_t)c * channel_stride;
         double sum = 0.0;
-        for_pairs(xc, xc, n, [&](float u, float) { sum = sum + (double)u; });
+        for_pairs<kC>(xc, xc, n, [&](float u, float) { sum = sum + (double)u; });
         const double mean = sum / (double)n;
         double sq = 0.0;
-        for_pairs(xc, xc, n, [&](float u, float) {
+        for_pairs<kC>(xc, xc, n, [&](float u, float) {
 #pragma clang fp contract(off)
             const double d = (double)u - mean;
             sq = sq + d * d;
@@ -130,8 +132,10 @@ __device__ inline double wave_score(const float* __restrict__ xw, int32_t num_ch
     return s;
 }
 
-// Tier-1 re-score by a workgroup of kG lanes (kG/64 wavefronts; every thread
-// calls it; red holds kG/64 doubles): lane l accumulates the terms
+// Tier-1 re-score by a group of kG lanes (kG/64 wavefronts; every thread of the
+// workgroup calls it, with its number tid within its group; red holds the
+// group's kG/64 doubles; a group that is not active only keeps the barriers):
+// lane l accumulates the terms
 // i = l + kG (4k + r) in four partial sums r = 0..3, combined as
 // (p0 + p1) + (p2 + p3), then a butterfly of lane shuffles in each wavefront,
 // then the wavefront sums in wavefront order.  Each partial sum holds at most
@@ -140,13 +144,13 @@ __device__ inline double wave_score(const float* __restrict__ xw, int32_t num_ch
 template <int kG>
 __device__ inline double group_score(const float* __restrict__ xw, int32_t num_channels,
                                      int64_t channel_stride, int64_t n, int64_t t,
-                                     const Weights& w, double* red) {
+                                     const Weights& w, double* red, int tid,
+                                     bool active = true) {
     constexpr int kWaves = kG / kWave;
-    const int tid = threadIdx.x;
     double s = 0.0;
     for (int32_t c = 0; c < num_channels; ++c) {
         const float* __restrict__ xc = xw + (int64_t)c * channel_stride;
-        const int64_t m = n - t;
+        const int64_t m = active ? n - t : 0;
         double p[4] = {0.0, 0.0, 0.0, 0.0};
         int64_t i = tid;
         // the operands of kAhead steps are loaded before they are added (in

@@ -253,10 +253,16 @@ int detect_within(const gpoeo_pd_desc* desc, const float* x, float* scores,
 
 // Kernel launchers; each returns hipGetLastError() after enqueueing.
 // var: [B][C][2] = population variance, mean |x| per window and channel.
-// fstat (nullable): [B*C][4] = mean, sum (x - mean)^2, sum |x - mean|, 0.
+// fstat (nullable): [B*C][4] = mean, sum (x - mean)^2, a bound of sum |x - mean|, 0.
+// sb (nullable): the selection state, cleared.
 hipError_t launch_window_stats(const Plan& p, const float* x, double* var, double* fstat,
-                               hipStream_t s);
-hipError_t launch_lag_score(const Plan& p, const float* x, double* part, hipStream_t s);
+                               const SelectBuffers* sb, hipStream_t s);
+// var (nullable; tiny plans only): the statistics of every sequence, computed beside the
+// scores.
+hipError_t launch_lag_score(const Plan& p, const float* x, double* part, double* var,
+                            hipStream_t s);
+hipError_t launch_lag_score_tiny(const Plan& p, const float* x, double* part, double* var,
+                                 hipStream_t s);
 // Sliding mode: full-block partials into `full`, cut-block partials into `cut`,
 // each [blocks*C + channel][block_chunks][lags_padded].
 hipError_t launch_lag_score_blocks(const Plan& p, const float* x, double* full, double* cut,

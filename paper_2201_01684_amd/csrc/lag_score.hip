@@ -253,47 +253,6 @@ void lag_score_kernel(ScoreArgs a) {
     for (int j = 0; j < kBT; ++j) out[j] = acc64[j];
 }
 
-// Tiny problems (one short trace, a few lags: the online case of Algorithm
-// 3): one workgroup of kTinyLags lanes per (sequence, block of kTinyLags lags,
-// chunk of kTinyChunk samples).  The chunk x[i0 .. i0 + kTinyChunk) and its
-// partners x[i0 + T0 .. i0 + T0 + kTinyChunk + kTinyLags) are staged in LDS
-// once (zeros past the window); lane l sums the pairs of lag T0 + l whose
-// partner lies in the window, as one fp32 run of at most kTinyChunk terms
-// (the same bound as the main kernel), and writes it as that chunk's partial.
-// Every load is issued at the start, so the kernel takes about one memory
-// round trip plus kTinyChunk steps.
-__global__ __launch_bounds__(kTinyLags) void lag_score_tiny_kernel(ScoreArgs a) {
-    __shared__ float xa[kTinyChunk];
-    __shared__ float xb[kTinyChunk + kTinyLags];
-    const int tid = threadIdx.x;
-    const int64_t task = blockIdx.x;
-    const int32_t k = (int32_t)(task % a.chunks);
-    const int64_t rest = task / a.chunks;
-    const int32_t blk = (int32_t)(rest % a.lag_blocks);
-    const int64_t bc = rest / a.lag_blocks;
-    const int64_t b = bc / a.num_channels;
-    const int32_t c = (int32_t)(bc % a.num_channels);
-    const float* __restrict__ xw = a.x + b * a.window_stride + (int64_t)c * a.channel_stride;
-    const int64_t n = a.n;
-    const int64_t i0 = (int64_t)k * kTinyChunk;
-    const int64_t t_blk = (int64_t)a.t0 + (int64_t)blk * kTinyLags;
-    for (int j = tid; j < kTinyChunk; j += kTinyLags) xa[j] = i0 + j < n ? xw[i0 + j] : 0.0f;
-    for (int j = tid; j < kTinyChunk + kTinyLags; j += kTinyLags) {
-        const int64_t idx = i0 + t_blk + j;
-        xb[j] = idx < n ? xw[idx] : 0.0f;
-    }
-    __syncthreads();
-    const int64_t t = t_blk + tid;
-    int64_t m = n - t - i0;                 // pairs (i0 + i, i0 + i + t) with i0 + i + t < n
-    m = m < 0 ? 0 : (m > kTinyChunk ? kTinyChunk : m);
-    float acc = 0.0f;
-    for (int i = 0; i < (int)m; ++i) {
-        const float d = xa[i] - xb[i + tid];
-        acc = __builtin_fmaf(d, d, acc);
-    }
-    a.part[(bc * a.chunks + k) * (int64_t)a.lags_padded + (t - a.t0)] = (double)acc;
-}
-
 template <int kBT, int kWPG>
 void launch_shifted(const Plan& p, const ScoreArgs& a, hipStream_t s) {
     const int64_t groups = (a.tasks + kWPG - 1) / kWPG;
@@ -344,16 +303,12 @@ ScoreArgs common(const Plan& p, const float* x) {
 
 }  // namespace
 
-hipError_t launch_lag_score(const Plan& p, const float* x, double* part, hipStream_t s) {
+hipError_t launch_lag_score(const Plan& p, const float* x, double* part, double* var,
+                            hipStream_t s) {
+    if (p.tiny) return launch_lag_score_tiny(p, x, part, var, s);
     ScoreArgs a = common(p, x);
     a.part = part;
-    if (p.tiny) {
-        const int64_t groups = p.num_windows * p.num_channels * p.lag_blocks * (int64_t)p.chunks;
-        hipLaunchKernelGGL(lag_score_tiny_kernel, dim3((unsigned)groups), dim3(kTinyLags), 0, s,
-                           a);
-    } else {
-        launch(p, a, s, p.lags_per_lane);
-    }
+    launch(p, a, s, p.lags_per_lane);
     return hipGetLastError();
 }
 

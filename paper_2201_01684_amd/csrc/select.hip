@@ -825,7 +825,8 @@ __global__ __launch_bounds__(kThreads) void rescore_kernel(SelectArgs a, Weights
         if (done) continue;
         const float* __restrict__ xw = a.x + table_off(a.tab, b, a.window_stride);
         const double v = group_score<kThreads>(xw, a.num_channels, a.channel_stride,
-                                               table_n(a.tab, b, a.n), t, w, red);
+                                               table_n(a.tab, b, a.n), t, w, red,
+                                               (int)threadIdx.x);
         if (threadIdx.x == 0) {
             a.s64[b * (int64_t)a.lags + j] = v;
             __threadfence();
@@ -857,52 +858,36 @@ __global__ __launch_bounds__(kThreads) void rescore_kernel(SelectArgs a, Weights
     }
 }
 
-// Clears the tier and queue bitmaps and the state of every window (a fill
-// kernel rather than a memset, so that the sequence stays capturable).
-__global__ __launch_bounds__(kThreads) void select_init_kernel(SelectBuffers sb, int64_t words,
-                                                               int64_t num_windows) {
-    const int64_t total = words * num_windows;
-    const int64_t step = (int64_t)gridDim.x * kThreads;
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < total; k += step) {
-        sb.tier1[k] = 0u;
-        sb.tier2[k] = 0u;
-        sb.queued1[k] = 0u;
-        sb.queued2[k] = 0u;
-    }
-    for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < num_windows; b += step) {
-        WinState z;
-        z.r_exact = 0.0;
-        z.done = 0;
-        z.r_queued = 0;
-        z.r_is_exact = 0;
-        z.rescored = 0;
-        z.tier2 = 0;
-        sb.state[b] = z;
-    }
-    if (blockIdx.x == 0 && (int)threadIdx.x < 2 * kPasses) sb.q_count[threadIdx.x] = 0;
-}
-
 // Re-scores the lags window b's rule marked in its queued bitmaps (and R), on
-// the LDS copies of the fused kernel: tier 1 by the whole workgroup (one lag at
-// a time), tier 2 and R by single lanes, with the same evaluations as
+// the LDS copies of the fused kernel: tier 1 by groups of kThreads lanes, one lag
+// each at a time, tier 2 and R by single lanes, with the same evaluations as
 // rescore_kernel.
 template <int kT>
 __device__ void rescore_window(const SelectArgs& a, const Weights& w, int64_t b, double* s,
                                uint32_t* t1, uint32_t* t2, const uint32_t* qd1,
                                const uint32_t* qd2, double* red) {
+    constexpr int kGroups = kT / kThreads;
+    constexpr int kAhead = kT > kThreads ? 8 : 32;          // samples ahead, in fewer registers
     const int tid = threadIdx.x;
+    const int group = tid / kThreads, lane = tid % kThreads;
     WinState* st = a.state + b;
     const float* __restrict__ xw = a.x + b * a.window_stride;
     for (int k = 0; k < a.words; ++k) {
-        // read by every thread before group_score's barriers let thread 0 set a bit of k
+        // read by every thread before group_score's barriers let a group set a bit of k
         uint32_t m = qd1[k] & ~t1[k];
         while (m) {
-            const int bit = __builtin_ctz(m);
-            m &= m - 1;
+            int bit = -1;                                   // this group's lag, if any
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                if (g == group && m) bit = __builtin_ctz(m);
+                m &= m - 1;
+            }
             const int64_t j = 32 * (int64_t)k + bit;
-            const double v = group_score<kT>(xw, a.num_channels, a.channel_stride, a.n,
-                                             a.tmin + j, w, red);
-            if (tid == 0) {
+            const double v = group_score<kThreads>(xw, a.num_channels, a.channel_stride, a.n,
+                                                   a.tmin + j, w,
+                                                   red + group * (kThreads / kWave), lane,
+                                                   bit >= 0);
+            if (lane == 0 && bit >= 0) {
                 s[j] = v;
                 atomicOr(&t1[k], 1u << bit);
                 atomicAdd(&st->rescored, 1);
@@ -916,13 +901,13 @@ __device__ void rescore_window(const SelectArgs& a, const Weights& w, int64_t b,
             const int bit = __builtin_ctz(m);
             m &= m - 1;
             const int64_t j = 32 * (int64_t)k + bit;
-            s[j] = exact_score(xw, a.num_channels, a.channel_stride, a.n, a.tmin + j, w);
+            s[j] = exact_score<kAhead>(xw, a.num_channels, a.channel_stride, a.n, a.tmin + j, w);
             st->tier2 = 1;
             atomicOr(&t2[k], 1u << bit);
         }
     }
     if (tid == 0 && st->r_queued && !st->r_is_exact) {
-        st->r_exact = exact_reference(xw, a.num_channels, a.channel_stride, a.n, w);
+        st->r_exact = exact_reference<kAhead>(xw, a.num_channels, a.channel_stride, a.n, w);
         st->tier2 = 1;
         st->r_is_exact = 1;
     }
@@ -930,7 +915,7 @@ __device__ void rescore_window(const SelectArgs& a, const Weights& w, int64_t b,
 
 struct FinishArgs {
     const double* part;      // lag-score chunk partials
-    double* var;             // [B][C][2], written here
+    double* var;             // [B][C][2], written here unless the score launch did
     float* scores;           // nullable
     int32_t t0, lags_padded, chunks;
 };
@@ -944,11 +929,15 @@ struct FinishArgs {
 // selection.  Same values, decisions and results as the separate kernels;
 // one launch instead of nine, for windows short enough that one workgroup
 // re-scores a lag quickly.
-__global__ __launch_bounds__(stats::kStatsThreads) void finish_kernel(SelectArgs a, FinishArgs f,
-                                                                     Weights w) {
-    constexpr int kT = stats::kStatsThreads;
+// kStats: the statistics here, as a kStatsThreads-wide workgroup; without them
+// (tiny plans compute them beside the scores) 512 threads halve the steps of
+// each scan (one window of 4096 samples, 1023 lags: 14.4 -> 12.4 us; 1024
+// threads 17.9 us, whose barriers and registers cost more).
+template <int kT, bool kStats>
+__global__ __launch_bounds__(kT) void finish_kernel(SelectArgs a, FinishArgs f, Weights w) {
+    static_assert(!kStats || kT == stats::kStatsThreads, "the statistics' visiting order");
     __shared__ Shared<kT> sh;
-    __shared__ double red[kT];
+    __shared__ double red[4 * kT / kWave];
     extern __shared__ double dyn[];
     double* s_l = dyn;
     uint32_t* bits = reinterpret_cast<uint32_t*>(dyn + a.lags);
@@ -960,20 +949,20 @@ __global__ __launch_bounds__(stats::kStatsThreads) void finish_kernel(SelectArgs
     const int64_t b = blockIdx.x;
     const float* __restrict__ xw = a.x + b * a.window_stride;
     const bool scores_only = (a.flags & GPOEO_PD_SCORES_ONLY) != 0;
-    if (!scores_only)
-        for (int32_t c = 0; c < a.num_channels; ++c) {
+    if constexpr (kStats)
+        for (int32_t c = 0; !scores_only && c < a.num_channels; ++c) {
             const stats::ChannelStats cs =
-                stats::channel_stats(xw + (int64_t)c * a.channel_stride, a.n, red, false);
+                stats::channel_stats<kT>(xw + (int64_t)c * a.channel_stride, a.n, red);
             if (tid == 0) {
                 const int64_t bc = b * a.num_channels + c;
                 f.var[2 * bc] = cs.var;
                 f.var[2 * bc + 1] = cs.absmean;
             }
         }
-    constexpr int L = stats::kFinalizeLags;
+    constexpr int L = kStats ? 4 : 2, kBatch = kStats ? 8 : 16;
     for (int32_t j = tid; j < a.lags; j += kT * L) {
         double v[L];
-        stats::finalize_lags(f.part, w, a.num_channels, b, a.n, (int64_t)a.tmin + j, kT,
+        stats::finalize_lags<L, kBatch>(f.part, w, a.num_channels, b, a.n, (int64_t)a.tmin + j, kT,
                              (int64_t)a.tmin + a.lags, f.t0, f.lags_padded, f.chunks, v);
 #pragma unroll
         for (int l = 0; l < L; ++l) {
@@ -1047,17 +1036,13 @@ hipError_t launch_finish(const Plan& p, const Weights& w, const float* x, double
     f.lags_padded = p.lags_padded;
     f.chunks = p.chunks;
     const size_t lds = (size_t)p.lags * sizeof(double) + 4 * (size_t)p.bitmap_words * 4;
-    hipLaunchKernelGGL(finish_kernel, dim3((unsigned)p.num_windows), dim3(stats::kStatsThreads),
-                       lds, s, a, f, w);
-    return hipGetLastError();
-}
-
-hipError_t launch_select_init(const Plan& p, const SelectBuffers& sb, hipStream_t s) {
-    const int64_t total = std::max<int64_t>((int64_t)p.bitmap_words * p.num_windows, p.num_windows);
-    int64_t groups = (total + kThreads - 1) / kThreads;
-    if (groups > 4096) groups = 4096;
-    hipLaunchKernelGGL(select_init_kernel, dim3((unsigned)groups), dim3(kThreads), 0, s, sb,
-                       (int64_t)p.bitmap_words, p.num_windows);
+    if (p.tiny)
+        hipLaunchKernelGGL((finish_kernel<512, false>), dim3((unsigned)p.num_windows), dim3(512),
+                           lds, s, a, f, w);
+    else
+        hipLaunchKernelGGL((finish_kernel<stats::kStatsThreads, true>),
+                           dim3((unsigned)p.num_windows), dim3(stats::kStatsThreads), lds, s, a, f,
+                           w);
     return hipGetLastError();
 }
 

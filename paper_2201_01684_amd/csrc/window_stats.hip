@@ -1,13 +1,13 @@
 // Window statistics and score finalisation.
 //
-// window_stats: per (window, channel), the population variance in fp64 by two
-//   passes (mean, then mean squared deviation), each a fixed-order workgroup
-//   reduction, and the mean absolute sample (which bounds how far any fp64
-//   evaluation order of the mean, and so of the variance, can stray).  The
-//   selection forms R = 2 * sum_c w_c * Var_c from it, the reference the
-//   relative-height candidate filter of Algorithm 1 is measured against in
-//   the lag domain.  For the FFT scores it also keeps the mean, the sum of
-//   squared deviations and the sum of absolute deviations.
+// window_stats: per (window, channel), the population variance in fp64, merged
+//   from groups of samples in a fixed order, and the mean absolute sample (which
+//   bounds how far any fp64 evaluation order of the mean, and so of the
+//   variance, can stray).  The selection forms R = 2 * sum_c w_c * Var_c from
+//   it, the reference the relative-height candidate filter of Algorithm 1 is
+//   measured against in the lag domain.  For the FFT scores it also keeps the
+//   mean, the sum of squared deviations and a bound of the sum of absolute
+//   ones.  It clears the window's selection state on the way.
 // finalize: per (window, lag), combines the fp64 chunk partials of every
 //   channel in ascending chunk order, divides by the N-T pairs and forms the
 //   weighted channel sum S(T) (the composite detection feature of Sec. 4.2).
@@ -19,13 +19,32 @@
 namespace gpoeo {
 namespace {
 
-__global__ __launch_bounds__(stats::kStatsThreads) void window_stats_kernel(
+// Clears the tier and queue bitmaps and the state of window b, and the queue
+// lengths with window 0's.
+__device__ __forceinline__ void clear_selection(const SelectBuffers& sb, int64_t b, int64_t words) {
+    for (int64_t k = threadIdx.x; k < words; k += blockDim.x) {
+        const int64_t i = b * words + k;
+        sb.tier1[i] = 0u;
+        sb.tier2[i] = 0u;
+        sb.queued1[i] = 0u;
+        sb.queued2[i] = 0u;
+    }
+    if (threadIdx.x == 0) sb.state[b] = WinState{};
+    if (b == 0 && (int)threadIdx.x < 2 * kPasses) sb.q_count[threadIdx.x] = 0;
+}
+
+// One workgroup per (window, channel); the first channel's also clears the
+// window's selection state (sb.state null: not needed).
+template <int kT>
+__global__ __launch_bounds__(kT) void window_stats_kernel(
     const float* __restrict__ x, double* __restrict__ var, int64_t n_all, int64_t window_stride,
-    int64_t channel_stride, int32_t num_channels, WindowTable tab, double* __restrict__ fstat) {
-    __shared__ double red[stats::kStatsThreads];
+    int64_t channel_stride, int32_t num_channels, WindowTable tab, double* __restrict__ fstat,
+    SelectBuffers sb, int64_t words) {
+    __shared__ double red[4 * kT / kWave];
     const int64_t bc = blockIdx.x;
     const int64_t b = bc / num_channels;
     const int32_t c = (int32_t)(bc % num_channels);
+    if (sb.state && c == 0) clear_selection(sb, b, words);
     const int64_t n = table_n(tab, b, n_all);
     if (n == 0) {   // empty slot of a window table
         if (threadIdx.x == 0) {
@@ -36,7 +55,7 @@ __global__ __launch_bounds__(stats::kStatsThreads) void window_stats_kernel(
     }
     const float* __restrict__ xw =
         x + table_off(tab, b, window_stride) + (int64_t)c * channel_stride;
-    const stats::ChannelStats st = stats::channel_stats(xw, n, red, fstat != nullptr);
+    const stats::ChannelStats st = stats::channel_stats<kT>(xw, n, red);
     if (threadIdx.x == 0) {
         var[2 * bc] = st.var;
         var[2 * bc + 1] = st.absmean;
@@ -47,6 +66,10 @@ __global__ __launch_bounds__(stats::kStatsThreads) void window_stats_kernel(
             fstat[4 * bc + 3] = 0.0;
         }
     }
+}
+
+__global__ __launch_bounds__(256) void select_init_kernel(SelectBuffers sb, int64_t words) {
+    clear_selection(sb, blockIdx.x, words);
 }
 
 // One workgroup per (window, block of 256 lags).  A window of a table scores
@@ -127,11 +150,31 @@ hipError_t launch_finalize_blocks(const Plan& p, const Weights& w, const double*
     return hipGetLastError();
 }
 
+// Few long sequences take 1024 threads each (96 of 100,003 samples: 29.6 -> 23.6
+// us); from one a CU on, 256 threads each stream as well and merge less (1024 of
+// 262,144: 227 -> 207 us; the suffix windows of a table: 54 -> 24 us).
+constexpr unsigned kStatsLongMaxGroups = 256;
+
 hipError_t launch_window_stats(const Plan& p, const float* x, double* var, double* fstat,
-                               hipStream_t s) {
-    const int64_t groups = p.num_windows * p.num_channels;
-    hipLaunchKernelGGL(window_stats_kernel, dim3((unsigned)groups), dim3(stats::kStatsThreads), 0, s, x,
-                       var, p.n, p.window_stride, p.channel_stride, p.num_channels, p.table, fstat);
+                               const SelectBuffers* sb, hipStream_t s) {
+    const dim3 groups((unsigned)(p.num_windows * p.num_channels));
+    const SelectBuffers clear = sb ? *sb : SelectBuffers{};
+    if (p.n > kFusedMaxN && !p.table.n && groups.x <= kStatsLongMaxGroups)
+        hipLaunchKernelGGL(window_stats_kernel<stats::kStatsLongThreads>, groups,
+                           dim3(stats::kStatsLongThreads), 0, s, x, var, p.n, p.window_stride,
+                           p.channel_stride, p.num_channels, p.table, fstat, clear,
+                           (int64_t)p.bitmap_words);
+    else
+        hipLaunchKernelGGL(window_stats_kernel<stats::kStatsThreads>, groups,
+                           dim3(stats::kStatsThreads), 0, s, x, var, p.n, p.window_stride,
+                           p.channel_stride, p.num_channels, p.table, fstat, clear,
+                           (int64_t)p.bitmap_words);
+    return hipGetLastError();
+}
+
+hipError_t launch_select_init(const Plan& p, const SelectBuffers& sb, hipStream_t s) {
+    hipLaunchKernelGGL(select_init_kernel, dim3((unsigned)p.num_windows), dim3(256), 0, s, sb,
+                       (int64_t)p.bitmap_words);
     return hipGetLastError();
 }
 
