@@ -973,7 +973,7 @@ struct FixArgs {
     int32_t wrap_lg;           // log2 of the head-tail transform (wrap correction), or -1
 };
 
-// One workgroup per window: lags whose score the FFT bound cannot place within
+// One workgroup per window and kFixLags lags: lags whose score the FFT bound cannot place within
 // tau0 / 2 of itself (the other half covers the rounding of the finalisation
 // and of the sequential evaluation) are re-scored by a wavefront in fp64 and
 // marked tier 1.  A score of exactly zero always lands here.
@@ -1000,19 +1000,19 @@ __global__ __launch_bounds__(kThreads) void fft_fixup_kernel(FixArgs a, Weights 
     const int wave = threadIdx.x >> 6;
     const float* __restrict__ xw = a.x + table_off(a.tab, b, a.window_stride);
     const int32_t nlags = tm - a.tmin + 1;
-    // wavefront w tests lags j0 + lane, j0 = 64 w + 256 k; the scores of
-    // kFixBatch consecutive k are loaded together (all in flight), then tested
-    constexpr int kFixBatch = 8;
-    for (int32_t jb = wave * kWave; jb < nlags; jb += kThreads * kFixBatch) {
+    // wavefront w tests lags j0 + lane, j0 = 64 w + 256 k past the workgroup's
+    // first; the scores of all kFixBatch k are loaded together, then tested
+    for (int64_t jb = (int64_t)blockIdx.y * kFixLags + wave * kWave; jb < nlags;
+         jb += (int64_t)gridDim.y * kFixLags) {
     double vb[kFixBatch];
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j = jb + r * kThreads + lane;
+        const int32_t j = (int32_t)jb + r * kThreads + lane;
         vb[r] = j < nlags ? a.s64[b * a.lags + j] : 0.0;
     }
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j0 = jb + r * kThreads;
+        const int32_t j0 = (int32_t)jb + r * kThreads;
         const int32_t j = j0 + lane;
         bool fix = false;
         if (j < nlags) {
@@ -1575,7 +1575,9 @@ hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, con
     a.tab = p.table;
     a.blocks = p.fft_blocks;
     a.wrap_lg = p.fft_wrap ? p.fft_wrap_log2 : -1;
-    hipLaunchKernelGGL(fft_fixup_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s, a,
+    hipLaunchKernelGGL(fft_fixup_kernel,
+                       dim3((unsigned)p.num_windows, (unsigned)std::min((p.lags + kFixLags - 1) / kFixLags, 65535)),
+                       dim3(kThreads), 0, s, a,
                        w);
     return hipGetLastError();
 }

@@ -66,6 +66,10 @@ constexpr int kMfmaMinChunkSteps = 64;
 constexpr int kSpecChunkBins = 2048;   // bins a workgroup of the spectral scan takes
 inline int fft_tile_log2(int lg) { return lg <= 2 * (kFftSmallTileLog2 - 1) ? kFftSmallTileLog2 : kFftTileLog2; }
 
+// Lags a workgroup of the score fix-ups tests: kFixBatch per thread.
+constexpr int kFixBatch = 8;
+constexpr int kFixLags = 256 * kFixBatch;
+
 struct Weights {
     float w[kMaxChannels];
 };

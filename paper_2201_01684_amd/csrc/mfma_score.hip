@@ -29,6 +29,7 @@
 // fp64 sums, the digit pairs left out, and the quantisation of inexact
 // sequences) is not within half the
 // selection's tier-0 width of its score.
+#include <algorithm>
 #include <cmath>
 
 #include "exact.h"
@@ -41,6 +42,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
+constexpr int64_t kPrepWideSeqs = 256;   // MI355X's CUs
 constexpr int kXcds = 8;   // MI355X: workgroups are dealt to its 8 XCDs in turn
 // Shift groups p + q = 2 .. 6 of the 13 digit-pair products kept, and the most
 // the three left out (p + q <= 1) add to one sample pair's product, 128^2 (1 + 2 * 256).
@@ -104,6 +106,7 @@ __device__ __forceinline__ void write_d(const MfmaArgs& a, int64_t s, int64_t n,
     }
 }
 
+template <int kT>
 __device__ double block_sum(double v, double* red) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_down(v, o);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -111,10 +114,11 @@ __device__ double block_sum(double v, double* red) {
     if (lane == 0) red[wave] = v;
     __syncthreads();
     double r = 0.0;
-    for (int w = 0; w < kThreads / kWave; ++w) r += red[w];
+    for (int w = 0; w < kT / kWave; ++w) r += red[w];
     return r;
 }
 
+template <int kT>
 __device__ float block_min(float v, float* red) {
     for (int o = kWave / 2; o > 0; o >>= 1) v = fminf(v, __shfl_down(v, o));
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -122,17 +126,20 @@ __device__ float block_min(float v, float* red) {
     if (lane == 0) red[wave] = v;
     __syncthreads();
     float r = red[0];
-    for (int w = 1; w < kThreads / kWave; ++w) r = fminf(r, red[w]);
+    for (int w = 1; w < kT / kWave; ++w) r = fminf(r, red[w]);
     return r;
 }
 
 // One workgroup per sequence.  Pass 1: mean, smallest and largest sample.
 // Pass 2: X_i, its digits, E = sum X_i^2, and whether every X_i 2^-s equals
 // x_i - c exactly.  Also zeroes the padding of the four digit planes (the
-// plane length and kMfmaPadL are multiples of 4 bytes, so are its stores).
-__global__ __launch_bounds__(kThreads) void mfma_prep_kernel(MfmaArgs a) {
-    __shared__ double red[kThreads / kWave];
-    __shared__ float redf[kThreads / kWave];
+// plane length and kMfmaPadL are multiples of 4 bytes, so are its stores).  With
+// fewer sequences than CUs a workgroup has 1024 threads (192 sequences of 65,537
+// samples: 51 -> 35 us).
+template <int kT>
+__global__ __launch_bounds__(kT) void mfma_prep_kernel(MfmaArgs a) {
+    __shared__ double red[kT / kWave];
+    __shared__ float redf[kT / kWave];
     const int64_t s = blockIdx.x;
     const float* __restrict__ xs = seq_ptr(a, s);
     const int64_t n = seq_n(a, s);
@@ -143,16 +150,16 @@ __global__ __launch_bounds__(kThreads) void mfma_prep_kernel(MfmaArgs a) {
         }
         return;
     }
-    // Each thread visits i = tid, tid + kThreads, ... in order; the samples of
+    // Each thread visits i = tid, tid + kT, ... in order; the samples of
     // kPrepBatch consecutive visits are loaded together (all in flight).
     constexpr int kPrepBatch = 8;
     double sum = 0.0;
     float mn = INFINITY, mx = -INFINITY;
     int64_t i1 = threadIdx.x;
-    for (; i1 + (kPrepBatch - 1) * kThreads < n; i1 += kPrepBatch * kThreads) {
+    for (; i1 + (kPrepBatch - 1) * kT < n; i1 += kPrepBatch * kT) {
         float v[kPrepBatch];
 #pragma unroll
-        for (int r = 0; r < kPrepBatch; ++r) v[r] = xs[i1 + r * kThreads];
+        for (int r = 0; r < kPrepBatch; ++r) v[r] = xs[i1 + r * kT];
 #pragma unroll
         for (int r = 0; r < kPrepBatch; ++r) {
             sum += (double)v[r];
@@ -160,15 +167,15 @@ __global__ __launch_bounds__(kThreads) void mfma_prep_kernel(MfmaArgs a) {
             mx = fmaxf(mx, v[r]);
         }
     }
-    for (; i1 < n; i1 += kThreads) {
+    for (; i1 < n; i1 += kT) {
         const float v = xs[i1];
         sum += (double)v;
         mn = fminf(mn, v);
         mx = fmaxf(mx, v);
     }
-    const double mean = block_sum(sum, red) / (double)n;
-    mn = block_min(mn, redf);
-    mx = -block_min(-mx, redf);
+    const double mean = block_sum<kT>(sum, red) / (double)n;
+    mn = block_min<kT>(mn, redf);
+    mx = -block_min<kT>(-mx, redf);
     const double c = (double)(float)mean;
     const double dev = fmax((double)mx - c, c - (double)mn);   // differences of fp32 values: exact
     int e = 0;
@@ -189,11 +196,11 @@ __global__ __launch_bounds__(kThreads) void mfma_prep_kernel(MfmaArgs a) {
         for (int k = 0; k < 4; ++k) v[k] = i + k < n ? xs[i + k] : 0.0f;
     };
     if (4 * (int64_t)threadIdx.x < n4) load4(4 * (int64_t)threadIdx.x, nxt);
-    for (int64_t i = 4 * (int64_t)threadIdx.x; i < n4; i += 4 * kThreads) {
+    for (int64_t i = 4 * (int64_t)threadIdx.x; i < n4; i += 4 * kT) {
         float cur[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) cur[k] = nxt[k];
-        if (i + 4 * kThreads < n4) load4(i + 4 * kThreads, nxt);
+        if (i + 4 * kT < n4) load4(i + 4 * kT, nxt);
         uint32_t word[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -226,13 +233,13 @@ __global__ __launch_bounds__(kThreads) void mfma_prep_kernel(MfmaArgs a) {
     // samples (a window of a table may be shorter than the plane)
     const int64_t pl = kMfmaPadL / 4;
     const int64_t pr = min(a.plane - kMfmaPadL - n4, (int64_t)kMfmaPadR) / 4;
-    for (int64_t k = threadIdx.x; k < 4 * (pl + pr); k += kThreads) {
+    for (int64_t k = threadIdx.x; k < 4 * (pl + pr); k += kT) {
         const int64_t p = k / (pl + pr), j = k % (pl + pr);
         const int64_t i = j < pl ? 4 * (j - pl) : n4 + 4 * (j - pl);
         *reinterpret_cast<uint32_t*>(d0 + p * a.plane + i) = 0u;
     }
-    const double etot = block_sum(ex, red);
-    const double ex_all = block_sum(exact ? 0.0 : 1.0, red);
+    const double etot = block_sum<kT>(ex, red);
+    const double ex_all = block_sum<kT>(exact ? 0.0 : 1.0, red);
     if (threadIdx.x == 0) {
         a.qstat[4 * s] = c;
         a.qstat[4 * s + 1] = (double)sc;
@@ -553,7 +560,8 @@ struct MfixArgs {
     WindowTable tab;
 };
 
-// One workgroup per window.  Per channel (X units): the rounding of E and of
+// One workgroup per window and kFixLags lags (24 windows of eight channels, 8190
+// lags: 21 us; a workgroup a window took 62).  Per channel (X units): the rounding of E and of
 // the edge sums (each within gamma_{N+1} E), of the three operations forming
 // D, and of the fp64 sum of the shift groups into r (5 additions per flush,
 // over terms whose magnitudes sum to at most (N - T) 2^62 1.008, because a
@@ -606,19 +614,19 @@ __global__ __launch_bounds__(kThreads) void mfma_fixup_kernel(MfixArgs a, Weight
     const int wave = threadIdx.x >> 6;
     const float* __restrict__ xw = a.x + table_off(a.tab, b, a.window_stride);
     const int32_t nlags = tm - a.tmin + 1;
-    // wavefront w tests lags j0 + lane, j0 = 64 w + 256 k; the scores of
-    // kFixBatch consecutive k are loaded together (all in flight), then tested
-    constexpr int kFixBatch = 8;
-    for (int32_t jb = wave * kWave; jb < nlags; jb += kThreads * kFixBatch) {
+    // wavefront w tests lags j0 + lane, j0 = 64 w + 256 k past the workgroup's
+    // first; the scores of all kFixBatch k are loaded together, then tested
+    for (int64_t jb = (int64_t)blockIdx.y * kFixLags + wave * kWave; jb < nlags;
+         jb += (int64_t)gridDim.y * kFixLags) {
     double vb[kFixBatch];
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j = jb + r * kThreads + lane;
+        const int32_t j = (int32_t)jb + r * kThreads + lane;
         vb[r] = j < nlags ? a.s64[b * a.lags + j] : 0.0;
     }
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j0 = jb + r * kThreads;
+        const int32_t j0 = (int32_t)jb + r * kThreads;
         const int32_t j = j0 + lane;
         bool fix = false;
         if (j < nlags) {
@@ -694,7 +702,11 @@ hipError_t launch_mfma_scores(const Plan& p, const float* x, double* qstat, int8
         a.scores = scores;
         a.w0 = w0;
     }
-    hipLaunchKernelGGL(mfma_prep_kernel, dim3((unsigned)a.seqs), dim3(kThreads), 0, s, a);
+    if (a.seqs <= kPrepWideSeqs && p.n > kFusedMaxN)
+        hipLaunchKernelGGL(mfma_prep_kernel<1024>, dim3((unsigned)a.seqs), dim3(1024), 0, s, a);
+    else
+        hipLaunchKernelGGL(mfma_prep_kernel<kThreads>, dim3((unsigned)a.seqs), dim3(kThreads), 0,
+                           s, a);
     hipLaunchKernelGGL(mfma_edge_kernel, dim3((unsigned)(2 * a.seqs)), dim3(kThreads), 0, s, a);
     const int64_t groups = (p.mfma_tiles + 3) / 4;
     const int64_t seqs8 = (a.seqs + kXcds - 1) / kXcds * kXcds;
@@ -734,7 +746,9 @@ hipError_t launch_mfma_fixup(const Plan& p, const Weights& w, const float* x,
     a.tau0 = kScoreRelBound;
     a.chunks = p.mfma_chunks;
     a.tab = p.table;
-    hipLaunchKernelGGL(mfma_fixup_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s, a,
+    hipLaunchKernelGGL(mfma_fixup_kernel,
+                       dim3((unsigned)p.num_windows, (unsigned)std::min((p.lags + kFixLags - 1) / kFixLags, 65535)),
+                       dim3(kThreads), 0, s, a,
                        w);
     return hipGetLastError();
 }
