@@ -24,7 +24,7 @@ LIB_NAME = "libgpoeo_pd.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
 
 SOURCES = ["api.cpp", "lag_score.hip", "lag_score_tiny.hip", "window_stats.hip", "select.hip", "rolling.hip",
-           "similarity.hip", "fft_score.hip", "fft_blocks.hip", "centred.hip", "mfma_score.hip", "noalloc.hip"]
+           "similarity.hip", "fft_score.hip", "fft_blocks.hip", "fft_spectrum.hip", "centred.hip", "mfma_score.hip", "noalloc.hip"]
 # The selection re-evaluates scores and thresholds as plain fp64 expressions
 # (one rounding per operation, as written); no multiply-add contraction there,
 # nor in the FFT, whose error bound assumes separately rounded products, nor in
@@ -35,6 +35,7 @@ EXTRA_FLAGS = {"select.hip": ["-ffp-contract=off"], "rolling.hip": ["-ffp-contra
                "lag_score_tiny.hip": ["-ffp-contract=off"],
                "similarity.hip": ["-ffp-contract=off"], "fft_score.hip": ["-ffp-contract=off"],
                "fft_blocks.hip": ["-ffp-contract=off"],
+               "fft_spectrum.hip": ["-ffp-contract=off"],
                "centred.hip": ["-ffp-contract=off"], "mfma_score.hip": ["-ffp-contract=off"]}
 ARCH = os.environ.get("GPOEO_PD_ARCH", "gfx950")
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

@@ -879,19 +879,20 @@ int make_spectral(const gpoeo_pd_desc* d, const gpoeo_pd_spectral_params* sp, Sp
     r->p.fft_pairs = (seqs + 1) / 2;
     int64_t n_z = 0, n_amp = 0;
     if (!gpoeo::mul_ok(r->p.fft_pairs, r->p.fft_len, &n_z) || n_z > (INT64_MAX / 64) ||
-        !gpoeo::mul_ok(seqs, r->p.fft_len / 2 + 1, &n_amp) || n_amp > (INT64_MAX / 16))
+        !gpoeo::mul_ok(seqs, gpoeo::spectral_bins(r->p), &n_amp) || n_amp > (INT64_MAX / 16))
         return GPOEO_PD_EINVAL;
     // one workgroup per chunk of a window's spectrum
     if (d->num_windows > ((int64_t(1) << 32) - 1) / 256 / gpoeo::spectral_chunks(r->p))
         return GPOEO_PD_EINVAL;
-    if (r->p.fft_m2 == 1) n_z = 0;                 // one workgroup per pair: no transform buffer
+    // one workgroup per pair: no transform buffer
+    if (r->p.fft_log2 <= gpoeo::kSpecSingleLog2) n_z = 0;
     size_t off = 0;
     r->off_var = off;
     off = gpoeo::align_up(off + (size_t)seqs * 2 * sizeof(double));
     r->off_fstat = off;
     off = gpoeo::align_up(off + (size_t)seqs * 4 * sizeof(double));
     r->off_tw = off;
-    off = gpoeo::align_up(off + (size_t)gpoeo::fft_twiddle_count(r->p) * 2 * sizeof(double));
+    off = gpoeo::align_up(off + (size_t)gpoeo::spectral_twiddles(r->p) * 2 * sizeof(double));
     r->off_z = off;
     off = gpoeo::align_up(off + (size_t)n_z * 2 * sizeof(double));
     r->off_amp = off;
@@ -930,8 +931,12 @@ int gpoeo_pd_spectral_candidates(const gpoeo_pd_desc* desc, const gpoeo_pd_spect
     double* var = reinterpret_cast<double*>(ws + r.off_var);
     double* fstat = reinterpret_cast<double*>(ws + r.off_fstat);
     const gpoeo::Weights w = weights_of(desc, r.p.num_channels);
-    if (gpoeo::launch_window_stats(r.p, x, var, fstat, nullptr, stream) != hipSuccess) return GPOEO_PD_EHIP;
-    if (gpoeo::launch_spectral(r.p, w, x, fstat, reinterpret_cast<double*>(ws + r.off_tw),
+    double* tw = reinterpret_cast<double*>(ws + r.off_tw);
+    if ((r.p.fft_log2 > gpoeo::kSpecSingleLog2
+             ? gpoeo::launch_spectrum_prepare(r.p, x, var, fstat, tw, stream)
+             : gpoeo::launch_window_stats(r.p, x, var, fstat, nullptr, stream)) != hipSuccess)
+        return GPOEO_PD_EHIP;
+    if (gpoeo::launch_spectral(r.p, w, x, fstat, tw,
                                reinterpret_cast<double*>(ws + r.off_z),
                                reinterpret_cast<double*>(ws + r.off_amp), ws + r.off_chunk,
                                params->c_peak,

@@ -790,65 +790,6 @@ __global__ __launch_bounds__(kTThreads) void spec_single_kernel(FftArgs a) {
     }
 }
 
-// Spectrum of a split transform: after the column kernel, forward row
-// transforms of row pairs (k1, L1 - k1), then the amplitudes at every
-// frequency k = k1 + L1 k2 <= L/2 (each written once: a self-paired row only
-// from its first slot).
-template <int kTile>
-__global__ __launch_bounds__(kTThreads) void spec_rows_kernel(FftArgs a) {
-    constexpr int kRegPoints = (1 << kTile) / kTThreads;
-    extern __shared__ double2 lds[];
-    const int64_t per = (int64_t(1) << (a.lg1 - 1)) + 1;
-    const int64_t wgs = (per + (1 << a.lgr) - 1) >> a.lgr;
-    const int64_t id = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t pair = id / wgs;
-    const int64_t g0 = (id % wgs) << a.lgr;
-    const uint32_t l1 = 1u << a.lg1;
-    const int lgs = a.lgr + 1;
-    const int slots = 1 << lgs;
-    const int l2 = 1 << a.lg2;
-    const int npts = l2 << lgs;
-    const double2* __restrict__ zp = a.z + pair * a.zstride;
-    auto k1_of = [&](int q, bool& valid, bool& self) -> uint32_t {
-        const int64_t g = g0 + (q >> 1);
-        valid = g < per;
-        const uint32_t ka = (uint32_t)g, kb = (l1 - (uint32_t)g) & (l1 - 1);
-        self = ka == kb;
-        return (q & 1) ? kb : ka;
-    };
-    {
-        double2 v[kRegPoints];
-#pragma unroll
-        for (int r = 0; r < kRegPoints; ++r) {
-            const int f = threadIdx.x + r * kTThreads;
-            bool valid, self;
-            const uint32_t k1 = k1_of(f & (slots - 1), valid, self);
-            v[r] = (valid && f < npts) ? zp[(int64_t)bitrev(k1, a.lg1) * l2 + (f >> lgs)]
-                                       : make_double2(0.0, 0.0);
-        }
-#pragma unroll
-        for (int r = 0; r < kRegPoints; ++r) {
-            const int f = threadIdx.x + r * kTThreads;
-            if (f < npts) lds[f] = v[r];
-        }
-    }
-    __syncthreads();
-    lds_fft_fwd<kTile>(lds, a.lg2, lgs, a.tw + a.tw_b);
-    const int64_t half_len = a.len / 2;
-    for (int f = threadIdx.x; f < npts; f += kTThreads) {
-        const int q = f & (slots - 1);
-        bool valid, self;
-        const uint32_t k1 = k1_of(q, valid, self);
-        if (!valid || ((q & 1) && self)) continue;
-        const uint32_t k2 = bitrev(f >> lgs, a.lg2);
-        const int64_t k = (int64_t)k1 + (int64_t)l1 * k2;
-        if (k > half_len) continue;
-        const uint32_t k2m = k1 == 0 ? ((l2 - k2) & (l2 - 1)) : (l2 - 1 - k2);
-        const int qm = self ? q : (q ^ 1);
-        write_amplitudes(a, pair, k, lds[f], lds[(bitrev(k2m, a.lg2) << lgs) + qm]);
-    }
-}
-
 // Absolute error bound of the computed D(T) of sequence s (any T), from the
 // norms of s and of the sequence it shares the transform with.
 //
@@ -1046,24 +987,34 @@ struct SpecChunk {
 };
 
 struct SpecSelArgs {
-    const double* amp;         // [S][half]: per-channel amplitudes
+    const double* amp;         // [S][stride]: per-channel amplitudes, by rows (rows > 0) or in order
     const double* fstat;       // [S][4]
     SpecChunk* chunk;          // [B][chunks]
     gpoeo_pd_spectral_result* out;
-    int64_t seqs, half, len;
+    int64_t seqs, half, len, stride;
     int32_t num_channels, tmin, tmax, k_max, lg, chunks;
+    int32_t lg1;               // log2 of the rows, or -1
+    int32_t scanned;           // spec_scan_kernel ran
     double c_peak;
 };
 
 constexpr int kCandCap = 1024;   // candidates collected per window
+// Spectra of more points are scanned by a launch of their own (8 windows of 20,000
+// samples: 67 us a call, 103 with the scan in the selection; of 8000: 54 either way).
+constexpr int64_t kSpecScanPoints = 8192;
 constexpr int kSpecChunk = kSpecChunkBins;
+constexpr int kSpecChunkLog2 = 11;
+constexpr int kSpecMaxChunks = (1 << (kFftMaxLog2 - 1)) / kSpecChunk + 1;
+static_assert(kSpecChunk == 1 << kSpecChunkLog2, "at least two entries of each of 1024 rows");
 
 // A(k) = sum_c w_c |X_c(k)| of window b, in channel order.
 __device__ __forceinline__ double spec_amp(const SpecSelArgs& a, const Weights& w, int64_t b,
                                            int64_t k) {
-    const double* __restrict__ amp = a.amp + b * a.num_channels * a.half + k;
+    const int64_t at =
+        a.lg1 < 0 ? k : (k & ((int64_t(1) << a.lg1) - 1)) * kSpecRow + (k >> a.lg1);
+    const double* __restrict__ amp = a.amp + b * a.num_channels * a.stride + at;
     double acc = 0.0;
-    for (int32_t c = 0; c < a.num_channels; ++c) acc += (double)w.w[c] * amp[c * a.half];
+    for (int32_t c = 0; c < a.num_channels; ++c) acc += (double)w.w[c] * amp[c * a.stride];
     return acc;
 }
 
@@ -1071,36 +1022,46 @@ __device__ __forceinline__ double spec_amp(const SpecSelArgs& a, const Weights& 
 // A(k) >= A(k+1)): their number, the largest, and the largest amplitude.  A
 // workgroup per chunk, so that few windows of long spectra fill the chip: the
 // selection of 300 windows of 131,073 bins and two channels took 462 us with
-// one workgroup a window, which wrote the channel sums back and read them twice.
+// one workgroup a window, which wrote the channel sums back and read them twice;
+// the scan and the selection take 210.
 __global__ __launch_bounds__(kThreads) void spec_scan_kernel(SpecSelArgs a, Weights w) {
     constexpr int kPer = kSpecChunk / kThreads;
-    __shared__ double s[kSpecChunk + 2];
+    __shared__ double s[kSpecChunk + 2 + (kSpecChunk + 2) / 32];
+    // (padded: entries a row apart would meet in one bank)
+    auto slot = [](int i) { return i + (i >> 5); };
     __shared__ double red[2][kThreads / kWave];
     __shared__ int32_t redi[kThreads / kWave];
     const int64_t b = blockIdx.x / a.chunks;
     const int32_t ch = (int32_t)(blockIdx.x % a.chunks);
     const int64_t k0 = (int64_t)ch * kSpecChunk;         // bins k0 .. k0 + kSpecChunk - 1
     const int tid = threadIdx.x;
+    // bin of a thread's r-th entry, in the order the amplitudes are stored
+    auto bin = [&](int r) {
+        const int i = tid + r * kThreads;
+        if (a.lg1 < 0) return i;
+        const int per = kSpecChunkLog2 - a.lg1;           // log2 of a row's entries in the chunk
+        return (i >> per) + ((i & ((1 << per) - 1)) << a.lg1);
+    };
     double v[kPer], e = 0.0;                             // all loads in flight
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        const int64_t k = k0 + tid + r * kThreads;
+        const int64_t k = k0 + bin(r);
         v[r] = k < a.half ? spec_amp(a, w, b, k) : 0.0;
     }
     const int64_t ke = tid == 0 ? k0 - 1 : k0 + kSpecChunk;   // the neighbours
     if (tid < 2 && ke >= 0 && ke < a.half) e = spec_amp(a, w, b, ke);
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) s[1 + tid + r * kThreads] = v[r];
-    if (tid < 2) s[tid == 0 ? 0 : kSpecChunk + 1] = e;
+    for (int r = 0; r < kPer; ++r) s[slot(1 + bin(r))] = v[r];
+    if (tid < 2) s[slot(tid == 0 ? 0 : kSpecChunk + 1)] = e;
     __syncthreads();
     double top = 0.0, most = 0.0;
     int32_t peaks = 0;
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        const int i = 1 + tid + r * kThreads;
+        const int i = 1 + bin(r);
         const int64_t k = k0 + i - 1;
         most = fmax(most, v[r]);
-        if (k >= 2 && k <= a.half - 2 && v[r] > s[i - 1] && v[r] >= s[i + 1]) {
+        if (k >= 2 && k <= a.half - 2 && v[r] > s[slot(i - 1)] && v[r] >= s[slot(i + 1)]) {
             ++peaks;
             top = fmax(top, v[r]);
         }
@@ -1143,20 +1104,33 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     __shared__ int32_t ncand;
     __shared__ int32_t flag;
     __shared__ gpoeo_pd_spectral_result res;
+    __shared__ int32_t list[kSpecMaxChunks];               // chunks to read again
+    __shared__ int32_t nlist;
     const int64_t b = blockIdx.x;
     const int tid = threadIdx.x;
     const SpecChunk* __restrict__ chunk = a.chunk + b * a.chunks;
     if (tid == 0) {
         ncand = 0;
         flag = 0;
+        nlist = 0;
     }
     for (int i = tid; i < (int)(sizeof(res) / 4); i += kThreads) reinterpret_cast<int32_t*>(&res)[i] = 0;
     // 1. the largest peak and the number of peaks
     double mx = 0.0;
     int32_t npk = 0;
-    for (int32_t i = tid; i < a.chunks; i += kThreads) {
-        mx = fmax(mx, chunk[i].top);
-        npk += (int32_t)chunk[i].peaks;
+    if (a.scanned) {
+        for (int32_t i = tid; i < a.chunks; i += kThreads) {
+            mx = fmax(mx, chunk[i].top);
+            npk += (int32_t)chunk[i].peaks;
+        }
+    } else {   // a short spectrum: here, instead of in a launch of its own
+        for (int64_t k = 2 + tid; k <= a.half - 2; k += kThreads) {
+            const double v = spec_amp(a, w, b, k);
+            if (v > spec_amp(a, w, b, k - 1) && v >= spec_amp(a, w, b, k + 1)) {
+                ++npk;
+                mx = fmax(mx, v);
+            }
+        }
     }
     red[tid] = mx;
     redi[tid] = npk;
@@ -1189,8 +1163,11 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     const double m = 4.0 * eps;
     const double thr = a.c_peak * top;
     // 3. candidates, and decisions too close to call
-    for (int32_t i = 0; i < a.chunks; ++i) {
-        if (chunk[i].most + m < a.c_peak * (top - m)) continue;   // the same for every thread
+    for (int32_t i = tid; i < a.chunks; i += kThreads)
+        if (!a.scanned || !(chunk[i].most + m < a.c_peak * (top - m))) list[atomicAdd(&nlist, 1)] = i;
+    __syncthreads();
+    for (int32_t li = 0; li < nlist; ++li) {
+        const int32_t i = list[li];
         const int64_t k0 = (int64_t)i * kSpecChunk;
         const int64_t k1 = min(k0 + (int64_t)kSpecChunk - 1, a.half - 2);
         for (int64_t k = max(k0, (int64_t)2) + tid; k <= k1; k += kThreads) {
@@ -1398,27 +1375,6 @@ void launch_twiddles(const FftArgs& a, double2* tw, hipStream_t s) {
     }
 }
 
-template <int kTile>
-void launch_spectrum(const Plan& p, const FftArgs& a, hipStream_t s) {
-    if (p.fft_m2 == 1) {
-        const size_t lds = sizeof(double2) * (size_t)p.fft_len;
-        hipLaunchKernelGGL(spec_single_kernel<kTile>, dim3((unsigned)p.fft_pairs), dim3(kTThreads),
-                           lds, s, a);
-        return;
-    }
-    const int64_t col_groups = p.fft_pairs * (p.fft_m2 / p.fft_cols);
-    const size_t lds_cols = sizeof(double2) * ((size_t)p.fft_m1 * p.fft_cols + p.fft_m1 / 2 +
-                                               (four_step_in_lds(a.lg1, a.lg2)
-                                                    ? (size_t)(p.fft_m1 + p.fft_m2) : 0));
-    const int64_t rp = int64_t(1) << a.lgr;
-    const size_t lds_rows = sizeof(double2) * 2 * rp * (size_t)p.fft_m2;
-    const int64_t row_groups = p.fft_pairs * ((p.fft_m1 / 2 + 1 + rp - 1) / rp);
-    hipLaunchKernelGGL((fft_cols_fwd_kernel<kTile>), dim3((unsigned)col_groups),
-                       dim3(kTThreads), lds_cols, s, a);
-    hipLaunchKernelGGL(spec_rows_kernel<kTile>, dim3((unsigned)row_groups), dim3(kTThreads),
-                       lds_rows, s, a);
-}
-
 }  // namespace
 
 int64_t spectral_chunks(const Plan& p) { return (p.fft_len / 2 + kSpecChunk) / kSpecChunk; }
@@ -1431,11 +1387,23 @@ hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, cons
                            int32_t k_max, gpoeo_pd_spectral_result* out, hipStream_t s) {
     FftArgs a = args_of(p, x, const_cast<double*>(fstat), nullptr, tw, z, nullptr);
     a.amp = amp;
-    launch_twiddles(a, reinterpret_cast<double2*>(tw), s);
-    if (fft_tile_log2(a.lg) == kFftSmallTileLog2)
-        launch_spectrum<kFftSmallTileLog2>(p, a, s);
-    else
-        launch_spectrum<kFftTileLog2>(p, a, s);
+    a.lg = p.fft_log2;
+    a.len = p.fft_len;
+    a.tw_a = 0;
+    const bool single = p.fft_log2 <= kSpecSingleLog2;
+    if (single)   // (launch_spectrum_prepare computed those of the others)
+        hipLaunchKernelGGL(fft_twiddle_kernel, dim3(8), dim3(256), 0, s,
+                           reinterpret_cast<double2*>(tw), p.fft_log2, 1, p.fft_log2, 0, (int64_t)0,
+                           (int64_t)0, (int64_t)0);
+    if (!single) {
+        if (launch_spectrum(p, x, fstat, tw, z, amp, s) != hipSuccess) return hipGetLastError();
+    } else if (p.fft_log2 <= kFftSmallTileLog2) {
+        hipLaunchKernelGGL(spec_single_kernel<kFftSmallTileLog2>, dim3((unsigned)p.fft_pairs),
+                           dim3(kTThreads), sizeof(double2) * (size_t)p.fft_len, s, a);
+    } else {
+        hipLaunchKernelGGL(spec_single_kernel<kFftTileLog2>, dim3((unsigned)p.fft_pairs),
+                           dim3(kTThreads), sizeof(double2) * (size_t)p.fft_len, s, a);
+    }
     SpecSelArgs sa;
     sa.amp = amp;
     sa.fstat = fstat;
@@ -1449,10 +1417,14 @@ hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, cons
     sa.k_max = k_max;
     sa.lg = p.fft_log2;
     sa.c_peak = c_peak;
+    sa.stride = spectral_bins(p);
+    sa.lg1 = single ? -1 : p.fft_log2 - kFftBlockLog2;
     sa.chunk = static_cast<SpecChunk*>(chunk);
     sa.chunks = (int32_t)spectral_chunks(p);
-    hipLaunchKernelGGL(spec_scan_kernel, dim3((unsigned)(p.num_windows * sa.chunks)),
-                       dim3(kThreads), 0, s, sa, w);
+    sa.scanned = p.fft_len > kSpecScanPoints;
+    if (sa.scanned)
+        hipLaunchKernelGGL(spec_scan_kernel, dim3((unsigned)(p.num_windows * sa.chunks)),
+                           dim3(kThreads), 0, s, sa, w);
     hipLaunchKernelGGL(spec_select_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s,
                        sa, w);
     return hipGetLastError();

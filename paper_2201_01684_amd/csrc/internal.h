@@ -63,8 +63,17 @@ constexpr int kMfmaFlush = 512;
 // partial cross terms a combination kernel adds in chunk order.
 constexpr int kMfmaTargetWaves = 4096;
 constexpr int kMfmaMinChunkSteps = 64;
+// Spectra of more than 2^kSpecSingleLog2 points: the amplitude of frequency k =
+// k1 + L1 k2 (L1 = L / 4096) at row k1, entry k2, of rows of kSpecRow entries.
+constexpr int kSpecSingleLog2 = 12;
+constexpr int kSpecRow = 2056;
 constexpr int kSpecChunkBins = 2048;   // bins a workgroup of the spectral scan takes
 inline int fft_tile_log2(int lg) { return lg <= 2 * (kFftSmallTileLog2 - 1) ? kFftSmallTileLog2 : kFftTileLog2; }
+
+// Few long sequences take 1024 statistics threads each (96 of 100,003 samples: 29.6
+// -> 23.6 us); from one a CU on, 256 threads each stream as well and merge less
+// (1024 of 262,144: 227 -> 207 us; the suffix windows of a table: 54 -> 24 us).
+constexpr int64_t kStatsLongMaxSeqs = 256;
 
 // Lags a workgroup of the score fix-ups tests: kFixBatch per thread.
 constexpr int kFixBatch = 8;
@@ -325,8 +334,22 @@ hipError_t launch_mfma_fixup(const Plan& p, const Weights& w, const float* x,
                              const SelectBuffers& sb, hipStream_t s);
 hipError_t launch_select_init(const Plan& p, const SelectBuffers& sb, hipStream_t s);
 // Spectral candidates (Algorithm 1's FFT front end) of every window: a plan
-// whose FFT geometry is that of L = 2^k >= N; amp: [B*C][L/2 + 1] fp64; chunk:
+// whose FFT length is that of L = 2^k >= N; amp: [B*C][spectral_bins] fp64; chunk:
 // spectral_chunk_bytes (the scan of spectral_chunks chunks of bins a window).
+// launch_spectrum: the amplitudes of spectra of more than one transform.
+inline int64_t spectral_bins(const Plan& p) {
+    return p.fft_log2 <= kSpecSingleLog2 ? p.fft_len / 2 + 1
+                                         : (int64_t)kSpecRow << (p.fft_log2 - kFftBlockLog2);
+}
+int64_t spectrum_twiddles(int32_t lg);
+inline int64_t spectral_twiddles(const Plan& p) {   // complex fp64 entries
+    return p.fft_log2 <= kSpecSingleLog2 ? p.fft_len / 2 : spectrum_twiddles(p.fft_log2);
+}
+// Statistics (as launch_window_stats) and twiddles in one launch, then the spectra.
+hipError_t launch_spectrum_prepare(const Plan& p, const float* x, double* var, double* fstat,
+                                   double* tw, hipStream_t s);
+hipError_t launch_spectrum(const Plan& p, const float* x, const double* fstat, const double* tw,
+                           double* z, double* amp, hipStream_t s);
 int64_t spectral_chunks(const Plan& p);
 size_t spectral_chunk_bytes(const Plan& p);
 hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, const double* fstat,

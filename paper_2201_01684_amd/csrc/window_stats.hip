@@ -150,16 +150,11 @@ hipError_t launch_finalize_blocks(const Plan& p, const Weights& w, const double*
     return hipGetLastError();
 }
 
-// Few long sequences take 1024 threads each (96 of 100,003 samples: 29.6 -> 23.6
-// us); from one a CU on, 256 threads each stream as well and merge less (1024 of
-// 262,144: 227 -> 207 us; the suffix windows of a table: 54 -> 24 us).
-constexpr unsigned kStatsLongMaxGroups = 256;
-
 hipError_t launch_window_stats(const Plan& p, const float* x, double* var, double* fstat,
                                const SelectBuffers* sb, hipStream_t s) {
     const dim3 groups((unsigned)(p.num_windows * p.num_channels));
     const SelectBuffers clear = sb ? *sb : SelectBuffers{};
-    if (p.n > kFusedMaxN && !p.table.n && groups.x <= kStatsLongMaxGroups)
+    if (p.n > kFusedMaxN && !p.table.n && groups.x <= kStatsLongMaxSeqs)
         hipLaunchKernelGGL(window_stats_kernel<stats::kStatsLongThreads>, groups,
                            dim3(stats::kStatsLongThreads), 0, s, x, var, p.n, p.window_stride,
                            p.channel_stride, p.num_channels, p.table, fstat, clear,
