@@ -103,7 +103,7 @@ bool launches_fit(const Plan& p) {
     const int64_t seqs = p.num_windows * (int64_t)p.num_channels;
     if (!fits(p.num_windows, 1024) || !fits(seqs, 256)) return false;
     if (p.fft) {
-        if (!fits(2 * seqs, 256)) return false;
+        if (!fits(2 * seqs + 8, 256)) return false;
         if (p.fft_blocks) {
             if (!fits(p.blk_pairs * std::max<int64_t>(p.blk_nb, p.blk_j), 512) ||
                 !fits(2 * p.blk_pairs * (kFftBlockSamples / 256) * ((p.blk_j + 15) / 16), 256))

@@ -233,6 +233,13 @@ __global__ __launch_bounds__(2 * kThreads) void fft_edge_kernel(FftArgs a) {
     __shared__ double tiles[2][kEdgeTile + kEdgeTile / 16];
     __shared__ double wsum[2][kEdgeWaves];
     const int64_t s = blockIdx.x;
+    if (s >= a.seqs) {   // the twiddles of the block transforms (one launch less)
+        const int e = (int)(s - a.seqs) * 2 * kThreads + (int)threadIdx.x;
+        double sn, cs;
+        sincospi(ldexp(2.0 * (double)e, -kFftBlockLog2), &sn, &cs);   // exact argument
+        a.tw_out[e] = make_double2(cs, -sn);
+        return;
+    }
     const int side = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
     double* tile = tiles[side];
     const int64_t b = s / a.num_channels;
@@ -1288,6 +1295,7 @@ FftArgs args_of(const Plan& p, const float* x, double* fstat, double* edge, doub
     a.fstat = fstat;
     a.edge = edge;
     a.tw = reinterpret_cast<const double2*>(tw);
+    a.tw_out = nullptr;
     a.z = reinterpret_cast<double2*>(z);
     a.part = part;
     a.amp = nullptr;
@@ -1494,10 +1502,10 @@ hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, doubl
         a.w0 = w0;
     }
     if (p.fft_blocks) {
-        hipLaunchKernelGGL(fft_twiddle_kernel, dim3(kFftBlockPoints / 2 / 256), dim3(256), 0, s,
-                           tw2, kFftBlockLog2, 1, kFftBlockLog2, 0, (int64_t)0, (int64_t)0,
-                           (int64_t)0);
-        hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)a.seqs), dim3(2 * kThreads), 0, s, a);
+        a.tw_out = tw2;
+        hipLaunchKernelGGL(fft_edge_kernel,
+                           dim3((unsigned)(a.seqs + kFftBlockPoints / 2 / (2 * kThreads))),
+                           dim3(2 * kThreads), 0, s, a);
         return launch_fft_blocks(p, FftBlockBuffers{tw, z, zw}, x, fstat, edge, part, a.s64,
                                  a.scores, w0, s);
     }
