@@ -51,7 +51,7 @@ CSRC = os.path.join(ROOT, "paper_2201_01684_amd", "csrc")
 COUNTERS = {"detect": (os.path.join(ROOT, "profiles", "lag_score_w3_counters.txt"),
                        os.path.join(CSRC, "lag_score.hip")),
             "fft": (os.path.join(ROOT, "profiles", "fft_stage_w3_counters.txt"),
-                    os.path.join(CSRC, "fft_score.hip")),
+                    os.path.join(CSRC, "fft_blocks.hip")),
             "mfma": (os.path.join(ROOT, "profiles", "mfma_xcorr_w3_counters.txt"),
                      os.path.join(CSRC, "mfma_score.hip"))}
 
