@@ -1404,7 +1404,8 @@ hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, cons
                            reinterpret_cast<double2*>(tw), p.fft_log2, 1, p.fft_log2, 0, (int64_t)0,
                            (int64_t)0, (int64_t)0);
     if (!single) {
-        if (launch_spectrum(p, x, fstat, tw, z, amp, s) != hipSuccess) return hipGetLastError();
+        const hipError_t err = launch_spectrum(p, x, fstat, tw, z, amp, s);
+        if (err != hipSuccess) return err;   // (hipGetLastError has been read and cleared)
     } else if (p.fft_log2 <= kFftSmallTileLog2) {
         hipLaunchKernelGGL(spec_single_kernel<kFftSmallTileLog2>, dim3((unsigned)p.fft_pairs),
                            dim3(kTThreads), sizeof(double2) * (size_t)p.fft_len, s, a);
