@@ -881,9 +881,6 @@ int make_spectral(const gpoeo_pd_desc* d, const gpoeo_pd_spectral_params* sp, Sp
     if (!gpoeo::mul_ok(r->p.fft_pairs, r->p.fft_len, &n_z) || n_z > (INT64_MAX / 64) ||
         !gpoeo::mul_ok(seqs, gpoeo::spectral_bins(r->p), &n_amp) || n_amp > (INT64_MAX / 16))
         return GPOEO_PD_EINVAL;
-    // one workgroup per chunk of a window's spectrum
-    if (d->num_windows > ((int64_t(1) << 32) - 1) / 256 / gpoeo::spectral_chunks(r->p))
-        return GPOEO_PD_EINVAL;
     // one workgroup per pair: no transform buffer
     if (r->p.fft_log2 <= gpoeo::kSpecSingleLog2) n_z = 0;
     size_t off = 0;

@@ -1002,6 +1002,7 @@ struct SpecSelArgs {
     int32_t num_channels, tmin, tmax, k_max, lg, chunks;
     int32_t lg1;               // log2 of the rows, or -1
     int32_t scanned;           // spec_scan_kernel ran
+    int64_t b0;                // first window of this scan launch
     double c_peak;
 };
 
@@ -1038,7 +1039,7 @@ __global__ __launch_bounds__(kThreads) void spec_scan_kernel(SpecSelArgs a, Weig
     auto slot = [](int i) { return i + (i >> 5); };
     __shared__ double red[2][kThreads / kWave];
     __shared__ int32_t redi[kThreads / kWave];
-    const int64_t b = blockIdx.x / a.chunks;
+    const int64_t b = a.b0 + blockIdx.x / a.chunks;
     const int32_t ch = (int32_t)(blockIdx.x % a.chunks);
     const int64_t k0 = (int64_t)ch * kSpecChunk;         // bins k0 .. k0 + kSpecChunk - 1
     const int tid = threadIdx.x;
@@ -1091,7 +1092,7 @@ __global__ __launch_bounds__(kThreads) void spec_scan_kernel(SpecSelArgs a, Weig
             c.most = fmax(c.most, red[1][i]);
             c.peaks += redi[i];
         }
-        a.chunk[blockIdx.x] = c;
+        a.chunk[b * a.chunks + ch] = c;
     }
 }
 
@@ -1431,9 +1432,13 @@ hipError_t launch_spectral(const Plan& p, const Weights& w, const float* x, cons
     sa.chunk = static_cast<SpecChunk*>(chunk);
     sa.chunks = (int32_t)spectral_chunks(p);
     sa.scanned = p.fft_len > kSpecScanPoints;
-    if (sa.scanned)
-        hipLaunchKernelGGL(spec_scan_kernel, dim3((unsigned)(p.num_windows * sa.chunks)),
-                           dim3(kThreads), 0, s, sa, w);
+    if (sa.scanned) {   // in several launches past HIP's 32-bit global size
+        const int64_t most = ((int64_t(1) << 32) - 1) / kThreads / sa.chunks;
+        for (sa.b0 = 0; sa.b0 < p.num_windows; sa.b0 += most)
+            hipLaunchKernelGGL(spec_scan_kernel,
+                               dim3((unsigned)(std::min(most, p.num_windows - sa.b0) * sa.chunks)),
+                               dim3(kThreads), 0, s, sa, w);
+    }
     hipLaunchKernelGGL(spec_select_kernel, dim3((unsigned)p.num_windows), dim3(kThreads), 0, s,
                        sa, w);
     return hipGetLastError();

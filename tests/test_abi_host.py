@@ -279,6 +279,11 @@ def test_fft_plan(lib):
     assert B.rolling_workspace_bytes(d, B.rolling_params()) > 0
 
 
+def test_spectra_of_more_chunks_than_one_launch_holds(lib):
+    d, _ = B.make_desc(1888572, 1, 31705, 1024, 31705, 578, 618)
+    assert B.spectral_workspace_bytes(d, B.spectral_params()) > 1 << 39
+
+
 def test_mfma_plan(lib):
     d, _ = good_desc(flags=B.MFMA_SCORES)
     info = B.describe_plan(d)
