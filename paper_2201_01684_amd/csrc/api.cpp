@@ -103,17 +103,20 @@ bool launches_fit(const Plan& p) {
     const int64_t seqs = p.num_windows * (int64_t)p.num_channels;
     if (!fits(p.num_windows, 1024) || !fits(seqs, 256)) return false;
     if (p.fft) {
-        if (!fits(2 * seqs + 8, 256)) return false;
-        if (p.fft_blocks) {
-            if (!fits(p.blk_pairs * std::max<int64_t>(p.blk_nb, p.blk_j), 512) ||
-                !fits(2 * p.blk_pairs * (kFftBlockSamples / 256) * ((p.blk_j + 15) / 16), 256))
-                return false;
-        } else {   // uniform transforms: one workgroup per tile of each pair
+        if (!fits(2 * seqs, 256)) return false;
+        if (p.fft_blocks &&
+            (!fits(p.blk_pairs * std::max<int64_t>(p.blk_nb, p.blk_j), 512) ||
+             !fits(2 * p.blk_pairs * (kFftBlockSamples / 256) * ((p.blk_j + 15) / 16), 256)))
+            return false;
+        // Uniform transforms: one workgroup per tile of each pair.  The same limit
+        // holds for a plan of sample blocks, so that which descriptors are valid
+        // does not depend on how their transforms are done.
+        if (!p.fft_table) {
             const int64_t per_pair =
                 p.fft_m2 == 1 ? 1 : std::max<int64_t>(p.fft_m2 / p.fft_cols, p.fft_m1 / 2 + 1);
             if (p.fft_pairs > kMax / 256 / per_pair) return false;
         }
-        if (p.fft_wrap) {
+        if (p.fft_wrap_log2 > 0) {
             int32_t m1, m2, cols;
             fft_geometry(p.fft_wrap_log2, &m1, &m2, &cols);
             const int64_t per_pair = std::max<int64_t>(m2 / cols, m1 / 2 + 1);

@@ -226,6 +226,7 @@ __device__ __forceinline__ double2 power_pair(double2 zk, double2 zm) {
 constexpr int kEdgeTile = 4096;
 constexpr int kEdgePer = kEdgeTile / kThreads;   // 16 terms per thread
 constexpr int kEdgeWaves = kThreads / kWave;
+constexpr int64_t kEdgeTwGroups = kFftBlockPoints / 2 / (2 * kThreads);   // W_4096^e, e < 2048
 
 __device__ __forceinline__ int edge_slot(int k) { return k + (k >> 4); }   // padded: no bank clash
 
@@ -233,13 +234,13 @@ __global__ __launch_bounds__(2 * kThreads) void fft_edge_kernel(FftArgs a) {
     __shared__ double tiles[2][kEdgeTile + kEdgeTile / 16];
     __shared__ double wsum[2][kEdgeWaves];
     const int64_t s = blockIdx.x;
-    if (s >= a.seqs) {   // the twiddles of the block transforms (one launch less)
-        const int e = (int)(s - a.seqs) * 2 * kThreads + (int)threadIdx.x;
+    if (a.tw_out && s < kEdgeTwGroups) {   // the twiddles of the block transforms, by the first
+        const int e = (int)s * 2 * kThreads + (int)threadIdx.x;
         double sn, cs;
         sincospi(ldexp(2.0 * (double)e, -kFftBlockLog2), &sn, &cs);   // exact argument
         a.tw_out[e] = make_double2(cs, -sn);
-        return;
     }
+    if (s >= a.seqs) return;
     const int side = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
     double* tile = tiles[side];
     const int64_t b = s / a.num_channels;
@@ -1509,8 +1510,7 @@ hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, doubl
     }
     if (p.fft_blocks) {
         a.tw_out = tw2;
-        hipLaunchKernelGGL(fft_edge_kernel,
-                           dim3((unsigned)(a.seqs + kFftBlockPoints / 2 / (2 * kThreads))),
+        hipLaunchKernelGGL(fft_edge_kernel, dim3((unsigned)std::max(a.seqs, kEdgeTwGroups)),
                            dim3(2 * kThreads), 0, s, a);
         return launch_fft_blocks(p, FftBlockBuffers{tw, z, zw}, x, fstat, edge, part, a.s64,
                                  a.scores, w0, s);

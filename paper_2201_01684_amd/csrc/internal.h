@@ -183,6 +183,8 @@ struct Plan {
     // the cross-correlation at shift Tmax - T of the first and the last M =
     // Tmax - W samples of the sequence.  A second transform of
     // 2^fft_wrap_log2 >= 2M points per pair computes it, and it is subtracted.
+    // (fft_wrap_log2 stays set, as do fft_m1, fft_m2 and fft_cols, when sample
+    // blocks take the transforms' place: launches_fit checks them.)
     bool fft_wrap;
     int32_t fft_wrap_m, fft_wrap_log2;
     // Scores from transforms of sample blocks: blk_nb blocks and blk_j lag

@@ -279,6 +279,25 @@ def test_fft_plan(lib):
     assert B.rolling_workspace_bytes(d, B.rolling_params()) > 0
 
 
+def test_valid_descriptors_do_not_depend_on_how_the_transforms_are_done(lib):
+    # the grids of one transform of N + Tmax points a pair exceed HIP's 32-bit global
+    # size: refused, also where sample blocks take the transforms' place ...
+    n = 3949544
+    d, _ = B.make_desc(8676, 8, n, 8 * n, n, 12, 27, flags=B.FFT_SCORES)
+    for size in (lambda: B.workspace_bytes(d), lambda: B.rolling_workspace_bytes(d, B.rolling_params())):
+        with pytest.raises(B.GpoeoError) as e:
+            size()
+        assert e.value.status == B.EINVAL
+    # ... and up to 2^23 - 1 sequences of one workgroup's transform are accepted
+    for windows, ok in ((8388607 // 7, True), (1 << 21, False)):
+        d, _ = B.make_desc(windows, 7, 64, 7 * 64, 64, 1, 16, flags=B.FFT_SCORES)
+        if ok:
+            assert windows * 7 >= 8388604 and B.workspace_bytes(d) > 0
+        else:
+            with pytest.raises(B.GpoeoError):
+                B.workspace_bytes(d)
+
+
 def test_spectra_of_more_chunks_than_one_launch_holds(lib):
     d, _ = B.make_desc(1888572, 1, 31705, 1024, 31705, 578, 618)
     assert B.spectral_workspace_bytes(d, B.spectral_params()) > 1 << 39
