@@ -196,12 +196,13 @@ __device__ inline double group_score(const float* __restrict__ xw, int32_t num_c
     return s;
 }
 
-// Half-width of the interval around the two-pass fp64 R that contains the
-// plain sequential evaluation.  Any evaluation order of the mean of N samples
-// errs by at most (N+1) u A (A = mean |x|); the second pass then sums
-// Var + dmean^2 exactly, up to (N+4) u relative.  Two orders thus differ by at
-// most 4 (N+4) u Var + 4.02 ((N+1) u A)^2 per channel, weighted and doubled
-// for R, plus the rounding of the weighted channel sum.
+// Half-width of the interval around the fp64 R of the window statistics that
+// contains the plain sequential evaluation.  That one's mean of N samples errs by
+// at most (N+1) u A (A = mean |x|), and its second pass sums Var + dmean^2, up to
+// (N+4) u relative; the statistics' variance errs by at most 3 (N+4) u relative
+// (channel_stats).  They thus differ by at most 4 (N+4) u Var + 4.02 ((N+1) u A)^2
+// per channel, weighted and doubled for R, plus the rounding of the weighted
+// channel sum.
 __device__ inline double reference_bound(const double* var2, int32_t num_channels, int64_t n,
                                   const Weights& w, double r) {
     const double u = 1.1102230246251565e-16;
