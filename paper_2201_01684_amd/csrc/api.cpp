@@ -24,11 +24,17 @@ constexpr size_t kAlign = 256;
 // 96 x 100003, T 12345 276 -> 222 us; 16 x 16384, T 4096 117 -> 78 us; 16 x
 // 262144, T 131072 610 -> 599 us.  Their sums over the blocks grow with Tmax
 // and win no longer past 2^17 lags (16 x 2^20, T 2^17 1.20 -> 1.20 ms, T 2^18
-// 1.78 -> 1.82 ms).  One to eight sequences would gain too (4 x 16384, T 4096
-// 117 -> 78 us), but the transform lengths and wrap term that
-// gpoeo_pd_describe_plan states for such calls are relied on; rolling
-// detection, which describes no plan, takes the blocks from one sequence on (one
-// window of 65536, T 8192: 307 -> 183 us), and for its suffix windows always.
+// 1.78 -> 1.82 ms).  A detection of one to eight sequences would gain too (4 x
+// 16384, T 4096 117 -> 78 us) but keeps the transform of N + Tmax points (or of N
+// and the wrap term), whose lengths gpoeo_pd_describe_plan promises for it.
+// Rolling detection describes no plan and takes the blocks from one sequence on
+// (one window of 65536, T 8192: 307 -> 183 us).  Its suffix windows, whose lengths
+// only the GPU knows, take them whatever Tmax is, as long transforms would all
+// have to be the longest one's: 7 suffixes of 0.6 to 1.3 million samples, T up to
+// 2^19, 0.42 ms of transforms, 0.74 ms with every pair of them at the length of
+// its own.  A transform of up to 2048 points is one workgroup's in any plan and
+// keeps nothing in memory (1024 windows of 512 samples, rolling: 534 us and 539
+// MiB of workspace by blocks, 311 us and 91 MiB so).
 constexpr int64_t kBlocksMinSeqs = 9;
 constexpr int32_t kBlocksMaxLag = 1 << 17;
 // Spectra of one launch, at most: larger batches run in several.  Smaller
@@ -203,8 +209,9 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
         }
         if (!set_fft_geometry(p, lg)) return GPOEO_PD_EINVAL;
         p->fft_blocks =
-            ragged || (d->num_windows * (int64_t)d->num_channels >= min_seqs &&
-                       lg > kFftSmallTileLog2 && d->tmax <= kBlocksMaxLag);
+            lg > kFftSmallTileLog2 &&
+            (ragged || (d->num_windows * (int64_t)d->num_channels >= min_seqs &&
+                        d->tmax <= kBlocksMaxLag));
         if (p->fft_blocks) {
             p->fft_wrap = false;
             p->fft_log2 = kFftBlockLog2;
@@ -369,8 +376,9 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
             return GPOEO_PD_EINVAL;
         n_tw = fft_twiddle_count(*p);
         if (p->fft_blocks) {   // spectra of the blocks and of the lag tiles
-            n_z = 2 * p->blk_pairs * p->blk_nb * kFftBlockSamples;
-            n_zw = 2 * p->blk_pairs * p->blk_j * kFftBlockSamples;
+            const int64_t per = p->blk_nb == 1 ? 0 : 2 * p->blk_pairs * kFftBlockSamples;
+            n_z = per * p->blk_nb;   // (none of pairs of one block)
+            n_zw = per * p->blk_j;
         }
         if (p->fft_wrap &&
             (!mul_ok(2 * p->fft_pairs, int64_t(1) << p->fft_wrap_log2, &n_zw) ||

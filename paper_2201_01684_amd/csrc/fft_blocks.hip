@@ -11,6 +11,7 @@
 //   blocks_fwd_kernel   X_b of every block, one 4096-point transform a workgroup
 //   blocks_corr_kernel  C_j along the blocks, every frequency on its own
 //   blocks_inv_kernel   r of m lags from R_j, and their D(T)
+// and a pair of sequences of one block each is done by the last of them alone.
 //
 // Against one transform of N + Tmax points split into columns and rows, the
 // spectra take two sweeps of 2N points instead of four of 2^k >= N + Tmax (or of
@@ -44,6 +45,7 @@ struct BlockArgs {
     double2* r;                // [2 pairs of this launch][jmax][kM]: 4 R_j(k)
     int64_t pair0;             // first pair of this launch
     int32_t nb, jmax;          // blocks and lag tiles of the longest window
+    int32_t one;               // the inverse launch does the pairs of one block alone
     int32_t step;              // workgroups per pair of the forward launch
 };
 
@@ -64,6 +66,85 @@ __device__ __forceinline__ Span span_of(const FftArgs& a, int64_t s) {
     return v;
 }
 
+// Passes of an inverse transform from the frequencies of this thread in v (the
+// forward one's backwards) to the points t + 512 r; the first barrier is after
+// the reads that filled v.
+__device__ __forceinline__ void inverse_passes(double2* lds, const Lanes& at, double2 (&v)[8],
+                                               const Twiddles& t1, const Twiddles& t2,
+                                               const Twiddles& t3) {
+    dft8<true, false>(v);
+    __syncthreads();                                              // all mirrors read
+    put8<1>(lds, at.s4, v);
+    wave_exchange();
+    get8<9>(lds, at.s3, v);
+    twiddle8<true>(v, t3);
+    dft8<true, false>(v);
+    put8<9>(lds, at.s3, v);
+    wave_exchange();
+    get8<73>(lds, at.s2, v);
+    twiddle8<true>(v, t2);
+    dft8<true, false>(v);
+    put8<73>(lds, at.s2, v);
+    __syncthreads();
+    get8<584>(lds, at.s1, v);
+    twiddle8<true>(v, t1);
+    dft8<true, false>(v);
+}
+
+// A pair whose sequences are one block each: its spectrum, the power spectra 4
+// |A|^2 + 4 i |B|^2 and their inverse transform, the autocorrelations of all its
+// lags (at most 1024), in one workgroup of the inverse launch; the other two leave
+// the pair out.  Neither spectra nor lag tiles pass through memory: rolling
+// detection of 1024 windows of 2048 samples 582 -> 387 us a call, of 8000 (suffixes
+// of 45 to 1260) 621 -> 545.  (In the forward launch, whose loop it slows, 256
+// windows of 8000 took 344 instead of 286 us; a launch of its own costs 5 us.)
+__device__ __forceinline__ void one_block(const BlockArgs& a, double2* lds, double2* tw512,
+                                          const Lanes& at, int64_t sa, int64_t sb) {
+    const Seq qa = seq_of(a.f, sa), qb = seq_of(a.f, sb);
+    const int c = at.t & 63;
+    double2 v[8], q[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        v[r] = make_double2(centred(qa, at.t + kT * r), centred(qb, at.t + kT * r));
+    if (at.t < 256) tw512[at.t] = a.f.tw[8 * at.t];
+    Twiddles t1, t2, t3;
+    t1.load(a.f.tw, at.t);
+    forward_first<true>(lds, at, v, t1);
+    __syncthreads();
+    forward_rest(lds, at, v, tw512);
+    __syncthreads();                                              // all points read
+#pragma unroll
+    for (int r = 4; r < 8; ++r) lds[at.sk + 584 * r] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool edge = r == 0 && at.t == 0;                    // k = 0, with k = 2048
+        const double2 zk = v[r];
+        const double2 zm = lds[edge ? 584 * 4 : at.sm + 584 * (7 - r)];
+        const double ux = zk.x + zm.x, uy = zk.y - zm.y, vx = zk.x - zm.x, vy = zk.y + zm.y;
+        v[r] = make_double2(ux * ux + uy * uy, vx * vx + vy * vy);
+        q[r] = v[r];
+        if (edge) {
+            v[r] = make_double2(4.0 * (zk.x * zk.x), 4.0 * (zk.y * zk.y));
+            q[r] = make_double2(4.0 * (zm.x * zm.x), 4.0 * (zm.y * zm.y));
+        }
+    }
+    __syncthreads();                                              // all mirrors read
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lds[r == 0 && at.t == 0 ? 584 * 4 : at.sm + 584 * (7 - r)] = q[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 4; r < 8; ++r) v[r] = lds[at.sk + 584 * r];
+    t3.load(tw512, 8 * (c & 7));
+    t2.load(tw512, c);
+    inverse_passes(lds, at, v, t1, t2, t3);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {                                 // lags t + 512 r up to 1024
+        write_d(a.f, sa, at.t + kT * r, v[r].x);
+        write_d(a.f, sb, at.t + kT * r, v[r].y);
+    }
+}
+
 // Workgroups of a forward launch (two fit a CU), if there are as many blocks
 // (1024 to 8192 differ by 3% on 1024 x 262144 and 256 x 8 x 131072).
 constexpr int64_t kFwdGroups = 4096;
@@ -82,6 +163,7 @@ __global__ __launch_bounds__(kT, 4) void blocks_fwd_kernel(BlockArgs a) {
     const Seq qa = seq_of(a.f, sa), qb = seq_of(a.f, sb);
     const int32_t na = span_of(a.f, sa).nb, nbb = span_of(a.f, sb).nb;
     const int32_t nb = max(na, nbb);
+    if (a.one && nb == 1) return;
     const Lanes at((int)threadIdx.x);
     float xa[4], xb[4];
     auto samples = [&](int32_t b) {
@@ -156,6 +238,7 @@ __global__ __launch_bounds__(kCorrThreads) void blocks_corr_kernel(BlockArgs a) 
     constexpr int kParts = kM / kCorrThreads;
     const int64_t sl = blockIdx.x / kParts;
     const Span sp = span_of(a.f, 2 * a.pair0 + sl);
+    if (a.one && sp.nb <= 1 && span_of(a.f, (2 * a.pair0 + sl) ^ 1).nb <= 1) return;
     const int32_t j0 = kOffset ? kJ * (int32_t)blockIdx.y : 0;
     if (j0 >= sp.j) return;
     const int k = (int)(blockIdx.x % kParts) * kCorrThreads + (int)threadIdx.x;
@@ -205,6 +288,7 @@ __global__ __launch_bounds__(kCorrThreads) void blocks_corr_kernel(BlockArgs a) 
 // all 4096 frequencies, its inverse transform (the passes of the forward one
 // backwards), and D(T) for T = 2048 j + n, 0 < n <= 2048.  The energies of
 // those lags are loaded before the transform (0.32 -> 0.29 ms).
+template <bool kOne>
 __global__ __launch_bounds__(kT, 4) void blocks_inv_kernel(BlockArgs a) {
     __shared__ double2 lds[kSlots];
     const int64_t pl = blockIdx.x / a.jmax;
@@ -213,6 +297,13 @@ __global__ __launch_bounds__(kT, 4) void blocks_inv_kernel(BlockArgs a) {
     const Span pa = span_of(a.f, sa), pb = span_of(a.f, sb);
     if (j >= max(pa.j, pb.j)) return;
     const Lanes at((int)threadIdx.x);
+    if constexpr (kOne) {
+        __shared__ double2 tw512[256];
+        if (max(pa.nb, pb.nb) == 1) {
+            one_block(a, lds, tw512, at, sa, sb);
+            return;
+        }
+    }
     const int c = at.t & 63;
     const double2* __restrict__ ra = a.r + ((2 * pl) * a.jmax + j) * (int64_t)kM + at.t;
     const double2* __restrict__ rb = ra + (int64_t)a.jmax * kM;
@@ -250,23 +341,7 @@ __global__ __launch_bounds__(kT, 4) void blocks_inv_kernel(BlockArgs a) {
     __syncthreads();
 #pragma unroll
     for (int r = 4; r < 8; ++r) v[r] = lds[at.sk + 584 * r];
-    dft8<true, false>(v);
-    __syncthreads();                                              // all mirrors read
-    put8<1>(lds, at.s4, v);
-    wave_exchange();
-    get8<9>(lds, at.s3, v);
-    twiddle8<true>(v, t3);
-    dft8<true, false>(v);
-    put8<9>(lds, at.s3, v);
-    wave_exchange();
-    get8<73>(lds, at.s2, v);
-    twiddle8<true>(v, t2);
-    dft8<true, false>(v);
-    put8<73>(lds, at.s2, v);
-    __syncthreads();
-    get8<584>(lds, at.s1, v);
-    twiddle8<true>(v, t1);
-    dft8<true, false>(v);
+    inverse_passes(lds, at, v, t1, t2, t3);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const double2 y = r == 0 && at.t == 0 ? v[4] : v[r];
@@ -304,10 +379,16 @@ hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const floa
     a.r = reinterpret_cast<double2*>(u.r);
     a.nb = p.blk_nb;
     a.jmax = p.blk_j;
+    a.one = p.blk_nb == 1 || p.fft_table;
     for (int64_t p0 = 0; p0 < p.fft_pairs; p0 += p.blk_pairs) {
         const int64_t pc = std::min(p.blk_pairs, p.fft_pairs - p0);
         a.pair0 = p0;
         a.step = (int32_t)std::min<int64_t>(p.blk_nb, (kFwdGroups + pc - 1) / pc);
+        const dim3 inv((unsigned)(pc * a.jmax));
+        if (a.one && p.blk_nb == 1) {
+            hipLaunchKernelGGL(blocks_inv_kernel<true>, inv, dim3(kT), 0, s, a);
+            continue;
+        }
         hipLaunchKernelGGL(blocks_fwd_kernel, dim3((unsigned)(pc * a.step)), dim3(kT), 0, s, a);
         const dim3 grid((unsigned)(2 * pc * (kM / kCorrThreads))), block(kCorrThreads);
         if (p.blk_j > 16)
@@ -321,7 +402,10 @@ hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const floa
             hipLaunchKernelGGL((blocks_corr_kernel<4, false>), grid, block, 0, s, a);
         else
             hipLaunchKernelGGL((blocks_corr_kernel<2, false>), grid, block, 0, s, a);
-        hipLaunchKernelGGL(blocks_inv_kernel, dim3((unsigned)(pc * a.jmax)), dim3(kT), 0, s, a);
+        if (a.one)
+            hipLaunchKernelGGL(blocks_inv_kernel<true>, inv, dim3(kT), 0, s, a);
+        else
+            hipLaunchKernelGGL(blocks_inv_kernel<false>, inv, dim3(kT), 0, s, a);
     }
     return hipGetLastError();
 }

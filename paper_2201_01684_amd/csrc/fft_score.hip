@@ -349,6 +349,7 @@ __global__ __launch_bounds__(kTThreads) void fft_single_kernel(FftArgs a) {
     extern __shared__ double2 lds[];
     const int64_t pair = blockIdx.x;
     const Seq qa = seq_of(a, 2 * pair), qb = seq_of(a, 2 * pair + 1);
+    if (qa.n <= 0 && qb.n <= 0) return;                    // empty slots of a window table
     const int lg = a.lg;
     const int len = 1 << lg;
     const double2* tw = a.tw + a.tw_a;

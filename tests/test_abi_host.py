@@ -303,6 +303,17 @@ def test_spectra_of_more_chunks_than_one_launch_holds(lib):
     assert B.spectral_workspace_bytes(d, B.spectral_params()) > 1 << 39
 
 
+@pytest.mark.parametrize("windows,channels,n,tmax,mib", [
+    (1024, 1, 256, 64, 50), (1024, 1, 512, 128, 99), (1024, 1, 1024, 256, 195),
+    (12, 200, 29, 4, 14), (1024, 1, 2048, 512, 389),
+])
+def test_rolling_workspace_of_short_traces(lib, windows, channels, n, tmax, mib):
+    # transforms of short suffix windows stay in one workgroup: no spectra in memory (before
+    # sample blocks these took as much as stated here)
+    d, _ = B.make_desc(windows, channels, n, n * channels, n, 2, tmax, flags=B.FFT_SCORES)
+    assert B.rolling_workspace_bytes(d, B.rolling_params()) <= mib << 20
+
+
 def test_mfma_plan(lib):
     d, _ = good_desc(flags=B.MFMA_SCORES)
     info = B.describe_plan(d)
