@@ -360,7 +360,7 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
             return GPOEO_PD_EINVAL;
     }
     if (n_part > (INT64_MAX / 16)) return GPOEO_PD_EINVAL;
-    int64_t n_fstat = 0, n_edge = 0, n_tw = 0, n_z = 0, n_zw = 0, n_wrap = 0;
+    int64_t n_fstat = 0, n_edge = 0, n_tw = 0, n_z = 0, n_zw = 0, n_wrap = 0, n_l1 = 0;
     int64_t n_dig = 0, n_qstat = 0, n_rpart = 0;
     if (p->mfma &&
         (!mul_ok(bc, 4, &n_qstat) || !mul_ok(bc, 2 * ((int64_t)d->tmax + 1), &n_edge) ||
@@ -375,6 +375,7 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
             !mul_ok(p->fft_pairs, p->fft_len, &n_z) || n_z > (INT64_MAX / 64))
             return GPOEO_PD_EINVAL;
         n_tw = fft_twiddle_count(*p);
+        n_l1 = 2 * p->fft_pairs * fft_l1_parts(*p);
         if (p->fft_blocks) {   // spectra of the blocks and of the lag tiles
             const int64_t per = p->blk_nb == 1 ? 0 : 2 * p->blk_pairs * kFftBlockSamples;
             n_z = per * p->blk_nb;   // (none of pairs of one block)
@@ -412,6 +413,8 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
     off = align_up(off + (size_t)n_zw * 2 * sizeof(double));
     p->off_wrap = off;                            // wrap terms
     off = align_up(off + (size_t)n_wrap * sizeof(double));
+    p->off_l1 = off;                              // partial sums of |y|
+    off = align_up(off + (size_t)n_l1 * sizeof(double));
     p->off_dig = off;                             // matrix-core scores: int8 digit planes
     off = align_up(off + (size_t)n_dig);
     p->off_qstat = off;                           // centre, scale, exactness, sum X^2
@@ -488,15 +491,16 @@ int run_plan(const gpoeo::Plan& p, const gpoeo::Weights& w, const float* x, floa
         double* zw = p.fft_wrap || p.fft_blocks ? reinterpret_cast<double*>(ws + p.off_zw)
                                                 : nullptr;
         double* wrap = p.fft_wrap ? reinterpret_cast<double*>(ws + p.off_wrap) : nullptr;
+        double* l1 = gpoeo::fft_l1_parts(p) ? reinterpret_cast<double*>(ws + p.off_l1) : nullptr;
         if (gpoeo::launch_fft_scores(p, x, fstat, reinterpret_cast<double*>(ws + p.off_edge),
                                      reinterpret_cast<double*>(ws + p.off_tw),
                                      reinterpret_cast<double*>(ws + p.off_z), c.part, zw,
-                                     wrap, c.s64, scores, w.w[0], stream) != hipSuccess)
+                                     wrap, l1, c.s64, scores, w.w[0], stream) != hipSuccess)
             return GPOEO_PD_EHIP;
         if (!mark(2)) return GPOEO_PD_EHIP;
         if ((!gpoeo::fft_fused_finalize(p, scores != nullptr) &&
              gpoeo::launch_finalize(p, w, c.part, c.s64, scores, stream) != hipSuccess) ||
-            gpoeo::launch_fft_fixup(p, w, x, fstat, c.s64, scores, c.sb, stream) !=
+            gpoeo::launch_fft_fixup(p, w, x, fstat, l1, c.s64, scores, c.sb, stream) !=
                 hipSuccess)
             return GPOEO_PD_EHIP;
     } else if (p.mfma) {

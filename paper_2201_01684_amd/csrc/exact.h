@@ -109,6 +109,23 @@ __device__ inline double wave_score(const float* __restrict__ xw, int32_t num_ch
         const int64_t m = n - t;
         double p[4] = {0.0, 0.0, 0.0, 0.0};
         int64_t i = lane;
+        // the operands of kAhead steps in flight together, added in the same order
+        // (without, every load waits for the one before: 37 lags of 2^21 samples 270 ->
+        // 21 ms a detection; eight steps 16, but fewer wavefronts fit)
+        constexpr int kAhead = 4;
+        for (; i + 64 * (4 * kAhead - 1) < m; i += 64 * 4 * kAhead) {
+            float u[4 * kAhead], v[4 * kAhead];
+#pragma unroll
+            for (int q = 0; q < 4 * kAhead; ++q) {
+                u[q] = xc[i + 64 * q];
+                v[q] = xc[i + 64 * q + t];
+            }
+#pragma unroll
+            for (int q = 0; q < 4 * kAhead; ++q) {
+                const double d = (double)u[q] - (double)v[q];
+                p[q & 3] = p[q & 3] + d * d;
+            }
+        }
         for (; i + 192 < m; i += 256) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {

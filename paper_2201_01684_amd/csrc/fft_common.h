@@ -14,6 +14,7 @@ struct FftArgs {
     const double* fstat;       // [S][4]: mean, sum y^2, sum |y|, unused (window statistics)
     double* edge;              // [S][tmax + 1]: E1(T) + E2(T)
     const double2* tw;         // twiddle tables
+    double* l1;                // column kernel: partial sums of |y| by wavefront, or null
     double2* tw_out;           // the edge kernel's extra workgroups write W_4096^e here, or null
     double2* z;                // [pairs][len]
     double* part;              // [S][lags]: D(T)

@@ -421,6 +421,7 @@ __global__ __launch_bounds__(kTThreads) void fft_cols_fwd_kernel(FftArgs a) {
     double2* tl = twl + (1 << (a.lg1 - 1));   // the four-step twiddles, after the pass ones
     FourStepCopy fc;
     if (lds4) fc.load(a);
+    double la = 0.0, lb = 0.0;
     if (rows4) {   // all loads of a thread in flight before its LDS writes
         constexpr int kRows = kRegPoints / 4;   // runs of four points a thread
         const int quads = cols >> 2;            // runs in a row of the tile
@@ -453,10 +454,16 @@ __global__ __launch_bounds__(kTThreads) void fft_cols_fwd_kernel(FftArgs a) {
             auto cv = [&](const Seq& q, float x, int64_t ii) {
                 return ii < q.n ? (double)x - q.mu : 0.0;
             };
-            lds[f + 0] = make_double2(cv(qa, va[k].x, i), cv(qb, vb[k].x, i));
-            lds[f + 1] = make_double2(cv(qa, va[k].y, i + 1), cv(qb, vb[k].y, i + 1));
-            lds[f + 2] = make_double2(cv(qa, va[k].z, i + 2), cv(qb, vb[k].z, i + 2));
-            lds[f + 3] = make_double2(cv(qa, va[k].w, i + 3), cv(qb, vb[k].w, i + 3));
+            const double2 y[4] = {make_double2(cv(qa, va[k].x, i), cv(qb, vb[k].x, i)),
+                                  make_double2(cv(qa, va[k].y, i + 1), cv(qb, vb[k].y, i + 1)),
+                                  make_double2(cv(qa, va[k].z, i + 2), cv(qb, vb[k].z, i + 2)),
+                                  make_double2(cv(qa, va[k].w, i + 3), cv(qb, vb[k].w, i + 3))};
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                lds[f + m] = y[m];
+                la += fabs(y[m].x);
+                lb += fabs(y[m].y);
+            }
         }
     } else {   // all loads of a thread in flight before its LDS writes
         TwiddleCopy<kTile> tc;
@@ -474,6 +481,20 @@ __global__ __launch_bounds__(kTThreads) void fft_cols_fwd_kernel(FftArgs a) {
         for (int r = 0; r < kRegPoints; ++r) {
             const int f = threadIdx.x + r * kTThreads;
             if (f < npts) lds[f] = v[r];
+            la += fabs(v[r].x);   // (0 past the tile)
+            lb += fabs(v[r].y);
+        }
+    }
+    if (a.l1) {   // sums of |y| by wavefront, for the fix-up's bound
+        for (int o = kWave / 2; o > 0; o >>= 1) {
+            la += __shfl_xor(la, o);
+            lb += __shfl_xor(lb, o);
+        }
+        const int64_t parts = groups * (kTThreads / kWave);
+        const int64_t part = (id % groups) * (kTThreads / kWave) + threadIdx.x / kWave;
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            a.l1[2 * pair * parts + part] = la;
+            a.l1[(2 * pair + 1) * parts + part] = lb;
         }
     }
     __syncthreads();
@@ -815,13 +836,13 @@ __global__ __launch_bounds__(kTThreads) void spec_single_kernel(FftArgs a) {
 // energies E - head and E - tail are sums of at most 2N + 2 rounded terms
 // (g_{2N+2} E each) plus the additions of the assembly, and centring in fp64
 // moves D by at most 4u sqrt(D E) + 4 u^2 E <= 2u D + 3u E.  The result is
-// doubled as a margin.
-__device__ double fft_bound(const double* fstat, int64_t s, int64_t seqs, int64_t n, int lg) {
+// doubled as a margin.  la and lb: |y_a|_1 and |y_b|_1, or bounds of them.
+__device__ double fft_bound(const double* fstat, int64_t s, int64_t seqs, int64_t n, int lg,
+                            double la, double lb) {
     const double u = 1.1102230246251565e-16;
-    const double ea = fstat[4 * s + 1], la = fstat[4 * s + 2];
+    const double ea = fstat[4 * s + 1];
     const int64_t o = s ^ 1;
     const double eb = o < seqs ? fstat[4 * o + 1] : 0.0;
-    const double lb = o < seqs ? fstat[4 * o + 2] : 0.0;
     const double ya = sqrt(ea), yb = sqrt(eb), zeta = sqrt(ea + eb);
     const double mu = 16.0 * u;
     const double g3 = 3.0 * u / (1.0 - 3.0 * u);
@@ -850,12 +871,12 @@ __device__ double fft_bound(const double* fstat, int64_t s, int64_t seqs, int64_
 // inverse transform by phi (1 + g3) ((|y_a|_1 + e1 sqrt(L) zeta)(|y_a| + e1 zeta)
 // + the same for b).  The sum bounds |cc_computed(s) - cc(s)|; D takes it
 // twice (D = ... - 2 (r_circ - cc)), with 1% margin, and the result is doubled.
-__device__ double fft_bound_wrap(const double* fstat, int64_t s, int64_t seqs, int lg) {
+__device__ double fft_bound_wrap(const double* fstat, int64_t s, int64_t seqs, int lg, double la,
+                                 double lb) {
     const double u = 1.1102230246251565e-16;
-    const double ea = fstat[4 * s + 1], la = fstat[4 * s + 2];
+    const double ea = fstat[4 * s + 1];
     const int64_t o = s ^ 1;
     const double eb = o < seqs ? fstat[4 * o + 1] : 0.0;
-    const double lb = o < seqs ? fstat[4 * o + 2] : 0.0;
     const double ya = sqrt(ea), yb = sqrt(eb), zeta = sqrt(ea + eb);
     const double mu = 16.0 * u;
     const double g3 = 3.0 * u / (1.0 - 3.0 * u);
@@ -921,35 +942,93 @@ struct FixArgs {
     WindowTable tab;
     int32_t blocks;            // transforms of sample blocks
     int32_t wrap_lg;           // log2 of the head-tail transform (wrap correction), or -1
+    const double* l1;          // split transforms: [S][l1_parts], partial sums of |y|; or null
+    int32_t l1_parts;
 };
+
+// sum_i |x_i - mean| of sequence s from the column kernel's partial sums, by the
+// whole workgroup.
+__device__ double centred_abs_sum(const FixArgs& a, int64_t s, double* red) {
+    if (s >= a.seqs) return 0.0;
+    double acc = 0.0;
+    for (int32_t k = threadIdx.x; k < a.l1_parts; k += kThreads) acc += a.l1[s * a.l1_parts + k];
+    for (int o = kWave / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    __syncthreads();                                       // red is free
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    acc = red[0];
+    for (int v = 1; v < kThreads / kWave; ++v) acc += red[v];
+    return acc;
+}
+
+// The bound of one channel's D(T) times its weight, with long transforms.
+__device__ double channel_bound(const FixArgs& a, const Weights& w, int32_t c, int64_t sq,
+                                int64_t n, double la, double lb) {
+    double e = fft_bound(a.fstat, sq, a.seqs, n, a.lg, la, lb);
+    if (a.wrap_lg >= 0) e += fft_bound_wrap(a.fstat, sq, a.seqs, a.wrap_lg, la, lb);
+    return (double)w.w[c] * e;
+}
 
 // One workgroup per window and kFixLags lags: lags whose score the FFT bound cannot place within
 // tau0 / 2 of itself (the other half covers the rounding of the finalisation
 // and of the sequential evaluation) are re-scored by a wavefront in fp64 and
 // marked tier 1.  A score of exactly zero always lands here.
+//
+// The bound of the long transforms takes the sums of absolute deviations, of
+// which the statistics give only sqrt(N) times the norm, up to several times as
+// much.  Where a lag would be re-scored by that and not with the least bound there
+// can be (no such term), the workgroup of a split transform takes the sums
+// themselves (a detection of 2^21 samples, three such lags: 7.3 -> 1.9 ms).  Up to 2048
+// samples the re-scores cost less than that test.
 __global__ __launch_bounds__(kThreads) void fft_fixup_kernel(FixArgs a, Weights w) {
-    __shared__ double abound;
+    __shared__ double abound, aleast;
+    __shared__ double red[kThreads / kWave];
     const int64_t b = blockIdx.x;
     const int64_t n = table_n(a.tab, b, a.n_all);
     if (n == 0) return;
     const int32_t tm = table_tmax(a.tab, b, a.tmax);
+    const int32_t nlags = tm - a.tmin + 1;
     if (threadIdx.x == 0) {
-        double acc = 0.0;
+        double acc = 0.0, least = 0.0;
         for (int32_t c = 0; c < a.num_channels; ++c) {
-            const int64_t sq = b * a.num_channels + c;
-            double e = a.blocks ? fft_bound_blocks(a.fstat, sq, a.seqs, n)
-                                : fft_bound(a.fstat, sq, a.seqs, n, a.lg);
-            if (a.wrap_lg >= 0) e += fft_bound_wrap(a.fstat, sq, a.seqs, a.wrap_lg);
-            acc += (double)w.w[c] * e;
+            const int64_t sq = b * a.num_channels + c, o = sq ^ 1;
+            acc += a.blocks ? (double)w.w[c] * fft_bound_blocks(a.fstat, sq, a.seqs, n)
+                            : channel_bound(a, w, c, sq, n, a.fstat[4 * sq + 2],
+                                            o < a.seqs ? a.fstat[4 * o + 2] : 0.0);
+            if (a.l1) least += channel_bound(a, w, c, sq, n, 0.0, 0.0);
         }
         abound = acc * (1.0 + 1e-12);
+        aleast = least;
+    }
+    if (a.l1) {
+        __syncthreads();
+        const double most = abound, least = aleast;
+        bool open = false;
+        for (int64_t j = (int64_t)blockIdx.y * kFixLags + threadIdx.x; j < nlags;
+             j += (int64_t)gridDim.y * kFixLags)
+#pragma unroll
+            for (int r = 0; r < kFixBatch; ++r)
+                if (j + r * kThreads < nlags) {
+                    const double lim = 0.5 * a.tau0 * a.s64[b * a.lags + j + r * kThreads] *
+                                       (double)(n - a.tmin - j - r * kThreads);
+                    open = open || (!(most <= lim) && least <= lim);
+                }
+        if (__syncthreads_or(open)) {
+            double acc = 0.0;
+            for (int32_t c = 0; c < a.num_channels; ++c) {
+                const int64_t sq = b * a.num_channels + c;
+                const double la = centred_abs_sum(a, sq, red);
+                const double lb = centred_abs_sum(a, sq ^ 1, red);
+                acc += channel_bound(a, w, c, sq, n, la, lb);
+            }
+            if (threadIdx.x == 0) abound = acc * (1.0 + 1e-12);
+        }
     }
     __syncthreads();
     const double ab = abound;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const float* __restrict__ xw = a.x + table_off(a.tab, b, a.window_stride);
-    const int32_t nlags = tm - a.tmin + 1;
     // wavefront w tests lags j0 + lane, j0 = 64 w + 256 k past the workgroup's
     // first; the scores of all kFixBatch k are loaded together, then tested
     for (int64_t jb = (int64_t)blockIdx.y * kFixLags + wave * kWave; jb < nlags;
@@ -960,16 +1039,21 @@ __global__ __launch_bounds__(kThreads) void fft_fixup_kernel(FixArgs a, Weights 
         const int32_t j = (int32_t)jb + r * kThreads + lane;
         vb[r] = j < nlags ? a.s64[b * a.lags + j] : 0.0;
     }
+    uint32_t fixes = 0;                                    // bit r: this lane's r-th lag
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j0 = (int32_t)jb + r * kThreads;
-        const int32_t j = j0 + lane;
+        const int32_t j = (int32_t)jb + r * kThreads + lane;
         bool fix = false;
         if (j < nlags) {
             const int64_t t = (int64_t)a.tmin + j;
             fix = !(ab / (double)(n - t) <= 0.5 * a.tau0 * vb[r]);
         }
-        uint64_t mask = __ballot(fix);
+        fixes |= fix ? 1u << r : 0u;
+    }
+#pragma unroll 1
+    for (int r = 0; r < kFixBatch; ++r) {
+        const int32_t j0 = (int32_t)jb + r * kThreads;
+        uint64_t mask = __ballot((fixes >> r) & 1u);
         while (mask) {
             const int k = __builtin_ctzll(mask);
             mask &= mask - 1;
@@ -1299,6 +1383,7 @@ FftArgs args_of(const Plan& p, const float* x, double* fstat, double* edge, doub
     a.edge = edge;
     a.tw = reinterpret_cast<const double2*>(tw);
     a.tw_out = nullptr;
+    a.l1 = nullptr;
     a.z = reinterpret_cast<double2*>(z);
     a.part = part;
     a.amp = nullptr;
@@ -1362,6 +1447,10 @@ int64_t twiddle_count_of(int lg) {
 }
 
 }  // namespace
+
+int32_t fft_l1_parts(const Plan& p) {
+    return p.fft_blocks || p.fft_m2 == 1 ? 0 : p.fft_m2 / p.fft_cols * (kTThreads / kWave);
+}
 
 // Complex fp64 entries of the twiddle tables of a plan.
 int64_t fft_twiddle_count(const Plan& p) {
@@ -1500,7 +1589,7 @@ void launch_wrap(const Plan& p, FftArgs aw, double2* tw, double2* zw, double* wr
 
 hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, double* edge,
                              double* tw, double* z, double* part, double* zw,
-                             double* wrap, double* s64, float* scores, float w0,
+                             double* wrap, double* l1, double* s64, float* scores, float w0,
                              hipStream_t s) {
     FftArgs a = args_of(p, x, fstat, edge, tw, z, part);
     double2* const tw2 = reinterpret_cast<double2*>(tw);
@@ -1531,6 +1620,7 @@ hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, doubl
         a.wrap_w = p.fft_len - p.n;
         a.wm = p.fft_wrap_m;
     }
+    a.l1 = l1;
     if (fft_tile_log2(a.lg) == kFftSmallTileLog2)
         launch_transforms<kFftSmallTileLog2>(a, p.fft_pairs, s);
     else
@@ -1539,7 +1629,7 @@ hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, doubl
 }
 
 hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                            double* s64, float* scores, const SelectBuffers& sb,
+                            const double* l1, double* s64, float* scores, const SelectBuffers& sb,
                             hipStream_t s) {
     FixArgs a;
     a.x = x;
@@ -1562,6 +1652,8 @@ hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, con
     a.tab = p.table;
     a.blocks = p.fft_blocks;
     a.wrap_lg = p.fft_wrap ? p.fft_wrap_log2 : -1;
+    a.l1 = l1;
+    a.l1_parts = fft_l1_parts(p);
     hipLaunchKernelGGL(fft_fixup_kernel,
                        dim3((unsigned)p.num_windows, (unsigned)std::min((p.lags + kFixLags - 1) / kFixLags, 65535)),
                        dim3(kThreads), 0, s, a,

@@ -214,7 +214,7 @@ struct Plan {
     int32_t bitmap_words;    // 32-bit words per window of the exactness bitmap
     // workspace layout (byte offsets, 256-byte aligned)
     size_t off_var, off_s64, off_bits, off_state, off_queue, off_part, off_cut;
-    size_t off_fstat, off_edge, off_tw, off_z, off_zw, off_wrap, off_dig, off_qstat,
+    size_t off_fstat, off_edge, off_tw, off_z, off_zw, off_wrap, off_l1, off_dig, off_qstat,
         off_rpart, bytes;
 };
 
@@ -291,6 +291,9 @@ hipError_t launch_finalize(const Plan& p, const Weights& w, const double* part, 
 // energies of the first and last N - T samples together; tw: twiddle tables;
 // z: [pairs][fft_len] complex fp64.  Writes D_c(T) into part ([B*C][lags]).
 int64_t fft_twiddle_count(const Plan& p);
+// l1: partial sums of |y| of each sequence from the column kernel, [2 pairs][fft_l1_parts]
+// (null if that is 0: transforms of one workgroup, or of sample blocks).
+int32_t fft_l1_parts(const Plan& p);
 // zw, wrap (wrap-corrected plans): [2][pairs][2^fft_wrap_log2] complex fp64
 // head and tail transforms; [B*C][M] fp64 wrap terms.  Null otherwise.
 // With one channel the transforms also do the finalisation: s64 and scores
@@ -311,13 +314,13 @@ hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const floa
                              float* scores, float w0, hipStream_t s);
 hipError_t launch_fft_scores(const Plan& p, const float* x, double* fstat, double* edge,
                              double* tw, double* z, double* part, double* zw,
-                             double* wrap, double* s64, float* scores, float w0,
+                             double* wrap, double* l1, double* s64, float* scores, float w0,
                              hipStream_t s);
 // After the finalisation: every lag whose FFT bound does not give the tier-0
 // guarantee is re-scored in fp64 (score, fp32 score and tier-1 bit).
 hipError_t launch_fft_fixup(const Plan& p, const Weights& w, const float* x, const double* fstat,
-                            double* s64, float* scores, const SelectBuffers& sb,
-                            hipStream_t s);
+                            const double* l1, double* s64, float* scores,
+                            const SelectBuffers& sb, hipStream_t s);
 
 // Matrix-core scores: per sequence the centre, scale and exactness (qstat
 // [S][4]), the digit planes, the edge sums and D(T) into `part`, or with one

@@ -624,10 +624,10 @@ __global__ __launch_bounds__(kThreads) void mfma_fixup_kernel(MfixArgs a, Weight
         const int32_t j = (int32_t)jb + r * kThreads + lane;
         vb[r] = j < nlags ? a.s64[b * a.lags + j] : 0.0;
     }
+    uint32_t fixes = 0;                                    // bit r: this lane's r-th lag
 #pragma unroll
     for (int r = 0; r < kFixBatch; ++r) {
-        const int32_t j0 = (int32_t)jb + r * kThreads;
-        const int32_t j = j0 + lane;
+        const int32_t j = (int32_t)jb + r * kThreads + lane;
         bool fix = false;
         if (j < nlags) {
             const int64_t t = (int64_t)a.tmin + j;
@@ -643,7 +643,12 @@ __global__ __launch_bounds__(kThreads) void mfma_fixup_kernel(MfixArgs a, Weight
             }
             fix = !(bound * (1.0 + 1e-12) / m <= 0.5 * a.tau0 * v);
         }
-        uint64_t mask = __ballot(fix);
+        fixes |= fix ? 1u << r : 0u;
+    }
+#pragma unroll 1
+    for (int r = 0; r < kFixBatch; ++r) {
+        const int32_t j0 = (int32_t)jb + r * kThreads;
+        uint64_t mask = __ballot((fixes >> r) & 1u);
         while (mask) {
             const int k = __builtin_ctzll(mask);
             mask &= mask - 1;

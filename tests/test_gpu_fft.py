@@ -247,3 +247,24 @@ def test_large_transforms(n, tmax, plan):
                                           dtype=ts.dtype)])
     o = oracle.score_list(x, lay, np.zeros(ts.size, dtype=np.int64), ts)
     check_fft_scores(g[0, ts - 2], o, f"n={n} Tmax={tmax}")
+
+
+@pytest.mark.parametrize("b,c", [(1, 1), (4, 1), (2, 3)])
+def test_no_lag_is_rescored_for_the_bound_of_the_absolute_sums(b, c):
+    """Pulses on a small noise: sum |y| is 0.16 of sqrt(N) times the norm of y, so the error
+    bound with that in its place (1.3 times what tier 0 allows at the period's lags) would
+    re-score lags that the bound with the sums themselves (0.6 times, 0.75 times at the
+    last lag) does not."""
+    import paper_2201_01684_amd as pkg
+    n, tmax = 16384, 4096
+    at = np.arange(n)
+    x = np.stack([np.stack([np.where((at + 7 * k) % 640 < 4, 400.0, 0.0)
+                            + np.random.default_rng(10 * j + k).normal(0, 0.2, n)
+                            for k in range(c)]) for j in range(b)]).astype(np.float32)
+    desc, keep = pkg.make_desc(b, c, n, n * c, n, 2, tmax, flags=fft_flag())
+    det = pkg.Detector(torch.from_numpy(x).to("cuda:0"), desc, keep)
+    det.run()
+    torch.cuda.synchronize()
+    res = det.results_numpy()
+    assert np.all(res["period"] == 640)
+    assert np.all(res["n_rescored"] == 0), res["n_rescored"]
