@@ -45,14 +45,17 @@
  * of its circular autocorrelation then carry the products of the first and
  * the last M = Tmax - (L - N) samples, which a second transform of at least
  * 2M points computes and which are subtracted (gpoeo_pd_describe_plan reports
- * both lengths).  A batch of more than eight sequences with lags up to 2^17
- * takes r from 4096-point transforms of blocks of 2048 samples instead: the
- * products of two blocks' spectra, summed over all pairs of blocks a given
- * number of blocks apart, give r at the lags of that distance
- * (gpoeo_pd_describe_plan then reports transforms of 4096 points).  Rolling
- * detection always does, over its suffix windows.  A rigorous absolute error
- * bound of each D_c(T), from the channel norms, decides which scores are within
- * 1e-6 relative of the exact value; every other lag (exact zeros included) is recomputed as an fp64 sum
+ * both lengths).  A batch of more than eight sequences of more than
+ * 2048 points (N + Tmax) with lags up to 2^17 takes r from 4096-point transforms
+ * instead: one where N + Tmax fits it, otherwise those of blocks of 2048 samples,
+ * whose products, summed over all pairs of blocks a given number of blocks
+ * apart, give r at the lags of that distance (gpoeo_pd_describe_plan then
+ * reports transforms of 4096 points).  Rolling detection does so from one
+ * sequence on, and for its suffix windows with any lags.  A call of up to eight
+ * sequences always has the transforms first described.  A rigorous absolute
+ * error bound of each D_c(T), from the channel norms, decides which scores are
+ * within 1e-6 relative of the exact value; every other lag (exact zeros
+ * included) is recomputed as an fp64 sum
  * before the selection, which then proceeds as above.  Selections equal those
  * of the direct scores.  Requires a transform of at most 2^22 points: N + Tmax
  * <= 2^22, or N <= 2^22 with a head-tail transform of at most min(2^20, L / 2)

@@ -218,6 +218,7 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
             p->fft_len = kFftBlockPoints;
             p->blk_nb = (int32_t)((d->n + kFftBlockSamples - 1) / kFftBlockSamples);
             p->blk_j = (d->tmax + kFftBlockSamples - 1) / kFftBlockSamples;
+            p->blk_whole = d->n + d->tmax <= kFftBlockPoints;
         }
     }
 
@@ -377,8 +378,8 @@ int make_plan(const gpoeo_pd_desc* d, Plan* p, bool ragged = false,
         n_tw = fft_twiddle_count(*p);
         n_l1 = 2 * p->fft_pairs * fft_l1_parts(*p);
         if (p->fft_blocks) {   // spectra of the blocks and of the lag tiles
-            const int64_t per = p->blk_nb == 1 ? 0 : 2 * p->blk_pairs * kFftBlockSamples;
-            n_z = per * p->blk_nb;   // (none of pairs of one block)
+            const int64_t per = p->blk_whole ? 0 : 2 * p->blk_pairs * kFftBlockSamples;
+            n_z = per * p->blk_nb;
             n_zw = per * p->blk_j;
         }
         if (p->fft_wrap &&

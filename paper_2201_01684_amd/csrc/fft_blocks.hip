@@ -11,7 +11,7 @@
 //   blocks_fwd_kernel   X_b of every block, one 4096-point transform a workgroup
 //   blocks_corr_kernel  C_j along the blocks, every frequency on its own
 //   blocks_inv_kernel   r of m lags from R_j, and their D(T)
-// and a pair of sequences of one block each is done by the last of them alone.
+// and a pair whose sequences fit one transform is done by the last of them alone.
 //
 // Against one transform of N + Tmax points split into columns and rows, the
 // spectra take two sweeps of 2N points instead of four of 2^k >= N + Tmax (or of
@@ -45,7 +45,7 @@ struct BlockArgs {
     double2* r;                // [2 pairs of this launch][jmax][kM]: 4 R_j(k)
     int64_t pair0;             // first pair of this launch
     int32_t nb, jmax;          // blocks and lag tiles of the longest window
-    int32_t one;               // the inverse launch does the pairs of one block alone
+    int32_t one;               // the inverse launch does the pairs of one transform alone
     int32_t step;              // workgroups per pair of the forward launch
 };
 
@@ -54,15 +54,18 @@ struct BlockArgs {
 struct Span {
     int64_t n;
     int32_t nb, j;
+    bool whole;                // n + Tmax points fit one transform
 };
 __device__ __forceinline__ Span span_of(const FftArgs& a, int64_t s) {
-    Span v = {0, 0, 0};
+    Span v = {0, 0, 0, true};
     if (s >= a.seqs) return v;
     const int64_t b = s / a.num_channels;
     v.n = table_n(a.tab, b, a.n_all);
     if (v.n <= 0) return v;
+    const int32_t tmax = min(table_tmax(a.tab, b, a.tmax), a.tmax);
     v.nb = (int32_t)((v.n + kM - 1) / kM);
-    v.j = (int32_t)((min(table_tmax(a.tab, b, a.tmax), a.tmax) + kM - 1) / kM);
+    v.j = (tmax + kM - 1) / kM;
+    v.whole = v.n + tmax <= kP;
     return v;
 }
 
@@ -91,25 +94,26 @@ __device__ __forceinline__ void inverse_passes(double2* lds, const Lanes& at, do
     dft8<true, false>(v);
 }
 
-// A pair whose sequences are one block each: its spectrum, the power spectra 4
-// |A|^2 + 4 i |B|^2 and their inverse transform, the autocorrelations of all its
-// lags (at most 1024), in one workgroup of the inverse launch; the other two leave
-// the pair out.  Neither spectra nor lag tiles pass through memory: rolling
-// detection of 1024 windows of 2048 samples 582 -> 387 us a call, of 8000 (suffixes
-// of 45 to 1260) 621 -> 545.  (In the forward launch, whose loop it slows, 256
-// windows of 8000 took 344 instead of 286 us; a launch of its own costs 5 us.)
-__device__ __forceinline__ void one_block(const BlockArgs& a, double2* lds, double2* tw512,
-                                          const Lanes& at, int64_t sa, int64_t sb) {
+// A pair whose sequences fit one transform (N + Tmax up to 4096 points): its
+// spectrum, the power spectra 4 |A|^2 + 4 i |B|^2 and their inverse transform, the
+// autocorrelations of all its lags, in one workgroup of the inverse launch; the
+// other two leave the pair out.  Neither spectra nor lag tiles pass through
+// memory: rolling detection of 1024 windows of 2048 samples 582 -> 393 us a call, of
+// 8000 (suffixes of 45 to 1260) 623 -> 449; detection of 4000 windows of 2100, T up
+// to 200, 322 -> 168.  (In the forward launch, whose loop it slows, 256 windows of
+// 8000 took 344 instead of 286 us; a launch of its own costs 5 us.)
+__device__ __forceinline__ void one_transform(const BlockArgs& a, double2* lds, double2* tw512,
+                                              const Lanes& at, int64_t sa, int64_t sb) {
     const Seq qa = seq_of(a.f, sa), qb = seq_of(a.f, sb);
     const int c = at.t & 63;
     double2 v[8], q[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 8; ++r)
         v[r] = make_double2(centred(qa, at.t + kT * r), centred(qb, at.t + kT * r));
     if (at.t < 256) tw512[at.t] = a.f.tw[8 * at.t];
     Twiddles t1, t2, t3;
     t1.load(a.f.tw, at.t);
-    forward_first<true>(lds, at, v, t1);
+    forward_first<false>(lds, at, v, t1);
     __syncthreads();
     forward_rest(lds, at, v, tw512);
     __syncthreads();                                              // all points read
@@ -139,7 +143,7 @@ __device__ __forceinline__ void one_block(const BlockArgs& a, double2* lds, doub
     t2.load(tw512, c);
     inverse_passes(lds, at, v, t1, t2, t3);
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {                                 // lags t + 512 r up to 1024
+    for (int r = 0; r < 3; ++r) {                                 // T <= 4096 / 3 < 1536
         write_d(a.f, sa, at.t + kT * r, v[r].x);
         write_d(a.f, sb, at.t + kT * r, v[r].y);
     }
@@ -161,9 +165,10 @@ __global__ __launch_bounds__(kT, 4) void blocks_fwd_kernel(BlockArgs a) {
     const int64_t pl = blockIdx.x / a.step;                       // pair within the launch
     const int64_t sa = 2 * (a.pair0 + pl), sb = sa + 1;
     const Seq qa = seq_of(a.f, sa), qb = seq_of(a.f, sb);
-    const int32_t na = span_of(a.f, sa).nb, nbb = span_of(a.f, sb).nb;
+    const Span pa = span_of(a.f, sa), pb = span_of(a.f, sb);
+    const int32_t na = pa.nb, nbb = pb.nb;
     const int32_t nb = max(na, nbb);
-    if (a.one && nb == 1) return;
+    if (a.one && pa.whole && pb.whole) return;
     const Lanes at((int)threadIdx.x);
     float xa[4], xb[4];
     auto samples = [&](int32_t b) {
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(kCorrThreads) void blocks_corr_kernel(BlockArgs a) 
     constexpr int kParts = kM / kCorrThreads;
     const int64_t sl = blockIdx.x / kParts;
     const Span sp = span_of(a.f, 2 * a.pair0 + sl);
-    if (a.one && sp.nb <= 1 && span_of(a.f, (2 * a.pair0 + sl) ^ 1).nb <= 1) return;
+    if (a.one && sp.whole && span_of(a.f, (2 * a.pair0 + sl) ^ 1).whole) return;
     const int32_t j0 = kOffset ? kJ * (int32_t)blockIdx.y : 0;
     if (j0 >= sp.j) return;
     const int k = (int)(blockIdx.x % kParts) * kCorrThreads + (int)threadIdx.x;
@@ -299,8 +304,8 @@ __global__ __launch_bounds__(kT, 4) void blocks_inv_kernel(BlockArgs a) {
     const Lanes at((int)threadIdx.x);
     if constexpr (kOne) {
         __shared__ double2 tw512[256];
-        if (max(pa.nb, pb.nb) == 1) {
-            one_block(a, lds, tw512, at, sa, sb);
+        if (pa.whole && pb.whole) {
+            one_transform(a, lds, tw512, at, sa, sb);
             return;
         }
     }
@@ -379,13 +384,13 @@ hipError_t launch_fft_blocks(const Plan& p, const FftBlockBuffers& u, const floa
     a.r = reinterpret_cast<double2*>(u.r);
     a.nb = p.blk_nb;
     a.jmax = p.blk_j;
-    a.one = p.blk_nb == 1 || p.fft_table;
+    a.one = p.blk_whole || p.fft_table;
     for (int64_t p0 = 0; p0 < p.fft_pairs; p0 += p.blk_pairs) {
         const int64_t pc = std::min(p.blk_pairs, p.fft_pairs - p0);
         a.pair0 = p0;
         a.step = (int32_t)std::min<int64_t>(p.blk_nb, (kFwdGroups + pc - 1) / pc);
         const dim3 inv((unsigned)(pc * a.jmax));
-        if (a.one && p.blk_nb == 1) {
+        if (p.blk_whole) {
             hipLaunchKernelGGL(blocks_inv_kernel<true>, inv, dim3(kT), 0, s, a);
             continue;
         }

@@ -188,8 +188,9 @@ struct Plan {
     bool fft_wrap;
     int32_t fft_wrap_m, fft_wrap_log2;
     // Scores from transforms of sample blocks: blk_nb blocks and blk_j lag
-    // tiles of the longest window, blk_pairs pairs a launch.
-    bool fft_blocks;
+    // tiles of the longest window, blk_pairs pairs a launch; blk_whole: every
+    // window and Tmax fit one transform (no spectra in memory).
+    bool fft_blocks, blk_whole;
     int32_t blk_nb, blk_j;
     int64_t blk_pairs;
     // Matrix-core scores: every sequence as four int8 digit planes of

@@ -314,6 +314,13 @@ def test_rolling_workspace_of_short_traces(lib, windows, channels, n, tmax, mib)
     assert B.rolling_workspace_bytes(d, B.rolling_params()) <= mib << 20
 
 
+@pytest.mark.parametrize("n,tmax,mib", [(2100, 200, 152), (3000, 50, 134), (2731, 1365, 310)])
+def test_fft_workspace_of_short_windows(lib, n, tmax, mib):
+    # (one transform of 4096 points in memory took as much as stated here)
+    d, _ = B.make_desc(4000, 1, n, n, n, 2, tmax, flags=B.FFT_SCORES)
+    assert B.workspace_bytes(d) <= mib << 20
+
+
 def test_mfma_plan(lib):
     d, _ = good_desc(flags=B.MFMA_SCORES)
     info = B.describe_plan(d)

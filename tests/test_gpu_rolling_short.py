@@ -1,8 +1,7 @@
-"""Rolling detection by FFT where its suffix windows are short: the suffix plan's two
-limits (longest window plus Tmax of 2048 points: one workgroup's transform of that length;
-windows of one block of 2048 samples: one workgroup's transform of 4096 points), and
-batches whose pairs hold one-block windows beside longer ones.  Against the oracle, as
-tests/test_gpu_rolling.py."""
+"""FFT scores of sequences short enough for one workgroup: transforms of up to 2048 points
+(N + Tmax), and one transform of 4096 points in place of sample blocks, in rolling
+detection (whose pairs may hold such a suffix window beside a longer one) and in
+detection.  Against the oracle, as tests/test_gpu_rolling.py and tests/test_gpu_fft.py."""
 import numpy as np
 import pytest
 
@@ -28,11 +27,11 @@ def batch(b, c, n, periods, seed=0):
     (5, 1, 29, 4, [3]),                         # transforms of 64 points
     (9, 1, 512, 128, [11, 40, 90]),             # 1024 points
     (7, 1, 1638, 410, [30, 77, 200, 300]),      # the suffix plan: 1638 + 410 = 2048 points
-    (7, 1, 1639, 410, [30, 77, 200, 300]),      # 2049: one block
-    (6, 1, 2048, 1024, [40, 400, 700, 900]),    # whole blocks, lag 1024
-    (5, 1, 2049, 1024, [40, 400, 700, 900]),    # one sample in the second block
+    (7, 1, 1639, 410, [30, 77, 200, 300]),      # 2049: one transform of 4096
+    (6, 1, 2731, 1365, [40, 400, 700, 900]),    # all of its 4096 points
+    (5, 1, 2732, 1365, [40, 400, 700, 900]),    # 4097: sample blocks for the longest
     (3, 3, 2048, 600, [50, 250]),               # an odd number of sequences
-    (11, 1, 9000, 2000, [9, 1500, 60, 390, 391]),   # one-block windows beside longer ones
+    (11, 1, 9000, 2000, [9, 1500, 60, 390, 391, 519, 521]),  # short beside longer windows
     (3, 5, 6000, 1400, [13, 1100, 380]),        # pairs across windows and channels
 ])
 def test_short_suffixes(b, c, n, tmax, periods):
@@ -42,14 +41,17 @@ def test_short_suffixes(b, c, n, tmax, periods):
     check(gpu_rolling(x, lay, "fft"), oracle.rolling(x, lay), f"{b}x{c}x{n} T<={tmax}")
 
 
-@pytest.mark.parametrize("n", [2046, 2048])
-def test_one_block_detection(n):
-    """A batch of one-block windows of more than 2048 points: exact ties, constant rows and
-    an odd count among them."""
+@pytest.mark.parametrize("n,tmax", [
+    (2046, 3), (2048, 1024),                    # 2049 points; a block
+    (2731, 1365), (2732, 1365),                 # 4096 points, 4097
+    (4076, 20), (4077, 20),
+])
+def test_one_transform_detection(n, tmax):
+    """A batch of short windows: exact ties, constant rows and an odd count among them."""
     from test_gpu_fft import fft_parity
     rows = [planted_trace(n, 37 + 50 * k, 5, seed=k, sigma=1.5) for k in range(8)]
     rows += [np.full(n, 4.0), planted_trace(n, 64, 4, seed=1, integer=True),
              np.where(np.arange(n) == 700, 1e4, 0.0)]
     x = np.stack(rows).astype(np.float32)
-    lay = oracle.Layout(len(rows), 1, n, n, n, 1, n // 2)
-    fft_parity(x, lay, f"one block, n={n}")
+    lay = oracle.Layout(len(rows), 1, n, n, n, 1, tmax)
+    fft_parity(x, lay, f"one transform, n={n} T<={tmax}")
