@@ -248,8 +248,9 @@ int gpoeo_pd_detect(const gpoeo_pd_desc* desc, const float* x, float* scores,
  * Returns GPOEO_PD_EINVAL as gpoeo_pd_detect does, GPOEO_PD_ETOOBIG when
  * the call needs more than GPOEO_PD_NOALLOC_MAX_WORKSPACE (gpoeo_pd_workspace_bytes,
  * or for FFT scores by sample blocks that of the long transforms, which then
- * take their place; both before launching anything), GPOEO_PD_EHIP if the array cannot be located or
- * a launch failed. */
+ * take their place: the selections are the same, scores may differ in their
+ * last bit; both before launching anything), GPOEO_PD_EHIP if the array cannot
+ * be located or a launch failed. */
 #define GPOEO_PD_NOALLOC_MAX_WORKSPACE ((size_t)64 << 20)
 
 int gpoeo_pd_detect_noalloc(const gpoeo_pd_desc* desc, const float* x, float* scores,

@@ -125,3 +125,26 @@ def test_noalloc_takes_the_long_transforms_where_blocks_do_not_fit():
     o, out = oracle.detect(x[3].cpu().numpy(), one)
     check_fft_scores(scores[3:4].cpu().numpy(), o, "noalloc")
     check_results(res[3:4], out, "noalloc")
+
+
+def test_several_launches():
+    """263 sequences of 2^20 samples: 132 pairs, whose spectra (32 MiB a pair, 4 GiB a launch)
+    take two launches, the second of four pairs and with a lone last sequence.  Windows on
+    both sides of the boundary against the oracle."""
+    b, n, tmin, tmax = 263, 1 << 20, 2040, 2060
+    rng = np.random.default_rng(77)
+    base = torch.from_numpy(planted_trace(n + 4 * b, 2050, 7, seed=7, sigma=3.0)).to("cuda:0")
+    x = torch.stack([base[4 * k:4 * k + n] * (1.0 + 0.01 * k) for k in range(b)])
+    x += torch.from_numpy(rng.normal(0, 1, n).astype(np.float32)).to("cuda:0")
+    import paper_2201_01684_amd as pkg
+    desc, keep = pkg.make_desc(b, 1, n, n, n, tmin, tmax, flags=fft_flag())
+    det = pkg.Detector(x, desc, keep)
+    assert (4 << 30) < det.ws_bytes < (4 << 30) + (100 << 20)      # 128 pairs' spectra, not 132
+    det.run()
+    torch.cuda.synchronize()
+    scores, res = det.scores.cpu().numpy(), det.results_numpy()
+    lay = oracle.Layout(1, 1, n, n, n, tmin, tmax)
+    for w in (0, 1, 254, 255, 256, 257, 260, 261, 262):
+        o, out = oracle.detect(x[w].cpu().numpy(), lay)
+        check_fft_scores(scores[w:w + 1], o, f"window {w}")
+        check_results(res[w:w + 1], out, f"window {w}")
