@@ -142,7 +142,10 @@ __device__ __forceinline__ void log_coeffs(const double (&mu)[G], const double (
 template <int G>
 __device__ __forceinline__ double responsibilities(const double (&l)[G], const Exp2Entry* table,
                                                    double (&e)[G]) {
-    if constexpr (G == 2) {
+    if constexpr (G == 1) {
+        e[0] = 1.0;
+        return 1.0;
+    } else if constexpr (G == 2) {
         const bool c = l[1] > l[0];
         const double x = gmm_exp2_nonpos(fmin(l[0], l[1]) - fmax(l[0], l[1]), table);
         e[0] = c ? x : 1.0;
@@ -335,8 +338,10 @@ __global__ __launch_bounds__(kThreads) void similarity_kernel(SimArgs a, Weights
     const int s = choose_segment(pairs, t);
     const int seg = tid / s, ls = tid % s, nseg = kThreads / s;
     if (tid == 0) any_fragile = 0;
-    if (tid < kExp2Table) exp2_table[tid] = kExp2[tid];
-    __syncthreads();
+    if constexpr (G > 1) {
+        if (tid < kExp2Table) exp2_table[tid] = kExp2[tid];
+        __syncthreads();
+    }
     bool fragile = false;
     double acc = 0.0, wsum = 0.0;
     for (int32_t c = 0; c < a.num_channels; ++c) {
