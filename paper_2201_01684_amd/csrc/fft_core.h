@@ -3,10 +3,13 @@
 // barrier (the last three passes stay inside a wavefront).  Included only by
 // translation units compiled with -ffp-contract=off.
 //
-// Rounding: a radix-8 pass is three radix-2 levels whose twiddles are exact or
-// a product with sqrt(1/2), then one multiplication with a twiddle accurate to 16
-// u.  That is less than three radix-2 stages with such twiddles, so the bounds
-// that charge a transform of 2^k points with k + 1 of those cover it.
+// Rounding, in units u of the norm: a radix-8 pass is three levels of additions
+// (u each) with exact turns or a product with sqrt(1/2) (3 u), then one
+// multiplication (2.3 u) with a twiddle accurate to 17 u (table entries within 2
+// ulp a component, so 4 u; a product adds the errors of both and 2.3 u, and w^7 is
+// made of two): 25 u at most.  The bounds charge three radix-2 stages of 21.7 u for
+// it, so a transform of 2^k points errs by less than half of the k + 1 stages that
+// they count.
 #pragma once
 
 #include "fft_common.h"
@@ -50,7 +53,7 @@ __device__ __forceinline__ void dft8(double2 (&v)[8]) {
 
 // The twiddles of a radix-8 pass, w^m for m = 1 .. 7: w, w^2 and w^4 from the
 // table (w = W_4096^e), the others as products of two of them or of one and a
-// product, each within the twiddle error 16 u that fft_bound assumes.
+// product, each within 17 u.
 struct Twiddles {
     double2 w1, w2, w4;
     __device__ __forceinline__ void load(const double2* __restrict__ tw, int e) {

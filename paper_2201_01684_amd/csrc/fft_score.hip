@@ -1240,7 +1240,8 @@ __global__ __launch_bounds__(kThreads) void spec_select_kernel(SpecSelArgs a, We
     const int32_t n_peaks = redi[0];
     __syncthreads();
     // 2. error bound of A (any k): the transform bound of each channel's pair
-    // (as for the FFT scores: phi sqrt(L) zeta, plus the separation), summed
+    // (as for the FFT scores: phi sqrt(L) zeta, plus the separation; more than
+    // twice what the passes of longer spectra err by, fft_spectrum.hip), summed
     // with the weights, plus the rounding of the amplitude and the channel sum
     const double u = 1.1102230246251565e-16;
     const double mu = 16.0 * u;

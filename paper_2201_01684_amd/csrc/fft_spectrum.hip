@@ -9,6 +9,13 @@
 // transforms up to L = 2^18, 16 times less at 2^22), and the amplitudes are
 // stored by rows, [k1][k2], which the selection's scan reads back in bins.
 //
+// Rounding, in units u of the norm (fft_core.h): four passes of the rows, 4 x 6 u
+// and 3 x 19 u; up to four passes of the columns, 6 u each and 19 u but for the
+// last; and the twiddles W_L^(n2 k1), powers of two table entries by repeated
+// squaring, within 48 u at W^(7 ..) (f[7] below: 23 u for each of its factors), and
+// their product, 2.3 u.  L = 2^18 has 81 + 31 + 50 = 162 u and 2^22 213 u at most;
+// the selection's bound charges (lg L + 1) 21.7 u, 412 and 499 u.
+//
 // Measured on 300 windows of two channels and 150,001 samples (L = 2^18):
 // 345 us for the columns (1.6 GB, 4.7 TB/s) and 560 us for the rows (1.9 GB, 3.4
 // TB/s: one workgroup a CU), where even splits of L with radix-2 passes between
