@@ -211,8 +211,8 @@ def fft_stage_bytes(wl, plan) -> float:
     blocks (transforms shorter than N + Tmax, and no wrap term): those of the
     blocks and of the lag tiles.  Otherwise each pair's complex fp64 transform
     written by the column kernel, read and written by the row kernel and read by
-    the inverse column kernel (none of that up to 2048 points, where a pair stays
-    in LDS), and with the wrap correction the first and last M samples read
+    the inverse column kernel (none of that up to 2048 points, or 4096 in a batch of
+    more than eight sequences, where a pair stays in LDS), and with the wrap correction the first and last M samples read
     again, the head and tail transforms written, read, the cross spectrum
     written and read back (six sweeps of the head-tail length), and the M wrap
     terms per sequence written and read."""
@@ -227,7 +227,7 @@ def fft_stage_bytes(wl, plan) -> float:
         total += 2 * 4 * s * m + 6 * 16 * pairs * plan["fft_wrap_len"] + 2 * 8 * s * m
     elif length < wl.n + wl.tmax:
         return float(total + s * block_spectra_bytes(wl.n, wl.tmax))
-    sweeps = 0 if length <= 2048 else 4
+    sweeps = 0 if length <= (4096 if s > 8 else 2048) else 4
     return float(total + sweeps * 16 * pairs * length)
 
 
@@ -723,14 +723,14 @@ def bench_spectral(args):
         det.run()
     ms, ev_ms, _ = timed_calls(det.run, args.steps)
     res = det.results_numpy()
-    # window statistics (two passes over the samples), the transforms (the
-    # samples once more; above 2048 points each pair's complex fp64 transform
+    # window statistics (one pass over the samples), the transforms (the
+    # samples once more; above 4096 points each pair's complex fp64 transform
     # written and read back), the amplitudes written and read by the selection
     seqs = wl.num_windows * wl.num_channels
     length = pow2_at_least(wl.n)
     half = length // 2 + 1
-    sweeps = 2 * 16 * ((seqs + 1) // 2) * length if length > 2048 else 0
-    spec_bytes = float(3 * 4 * seqs * wl.n + sweeps + 2 * 8 * seqs * half)
+    sweeps = 2 * 16 * ((seqs + 1) // 2) * length if length > 4096 else 0
+    spec_bytes = float(2 * 4 * seqs * wl.n + sweeps + 2 * 8 * seqs * half)
     roofline = call_roofline("spectral call: window statistics, column and row transforms, "
                              "amplitude selection", "hbm", spec_bytes, ev_ms,
                              {"bytes_per_launch": spec_bytes})
@@ -809,9 +809,10 @@ def bench_rolling(args):
     pairs_c = sum(c * lag_sum(n, tm) for n, tm in suffix if tm >= wl.tmin)
     if args.fft_scores:
         work = fft_stage_bytes(wl, pkg.describe_plan(desc))   # the whole-window pass
-        # suffix pass: every suffix by sample blocks of its own
+        # suffix pass: every suffix by sample blocks of its own, or one transform in LDS
         for n_j, tm in suffix:
-            work += c * (4 * n_j + 2 * 4 * tm + 3 * 8 * tm + block_spectra_bytes(n_j, tm))
+            spectra = block_spectra_bytes(n_j, tm) if n_j + tm > 4096 else 0
+            work += c * (4 * n_j + 2 * 4 * tm + 3 * 8 * tm + spectra)
         roofline = call_roofline("both FFT score passes (whole windows, then suffix windows, "
                                  "by sample blocks)", "hbm", work, ev_ms,
                                  {"bytes_per_launch": work})
