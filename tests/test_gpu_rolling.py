@@ -5,9 +5,8 @@ periods, the selected window and period, stability and the next sampling
 duration.  diff to float rounding, err within 1e-4 relative.  Each case runs
 with the direct scores, the FFT scores and the matrix-core scores (whose
 suffix pass reads the window table in every kernel); the FFT scores of the suffix
-pass give every pair of sequences the transform length its own suffixes need
-(length classes from 2^6 up), so the mixed batches below span several classes,
-both transform shapes (one workgroup, split) and, with an odd channel count,
+pass take every pair of sequences by the blocks of its own suffixes, or by one transform
+where they fit it, so the mixed batches below span both and, with an odd channel count,
 pairs whose two sequences come from different suffix windows.
 """
 import numpy as np
@@ -88,8 +87,8 @@ def test_rolling_reduced_workloads(name, kw, mode):
 
 
 def test_rolling_fft_periods_across_length_classes():
-    # periods from 12 to 3000 samples in one batch: suffix transforms from 2^6
-    # to 2^15 points; three channels, so pairs straddle suffix windows
+    # periods from 12 to 3000 samples in one batch: suffixes of 27 to 15,750 samples;
+    # three channels, so pairs straddle suffix windows
     n = 24000
     periods = [12, 40, 100, 333, 800, 1500, 3000]
     x = np.stack([np.stack([planted_trace(n, p, 5, seed=10 * p + c, sigma=0.5 + c)
