@@ -408,7 +408,7 @@ hipError_t launch_spectrum(const Plan& p, const float* x, const double* fstat, c
         case 9: launch_cols<9>(a, p.fft_pairs, s); break;
         default: launch_cols<10>(a, p.fft_pairs, s); break;
     }
-    hipLaunchKernelGGL(spectrum_rows_kernel, 
+    hipLaunchKernelGGL(spectrum_rows_kernel,
                        dim3((unsigned)std::min(p.fft_pairs << (a.lg1 - 1), kRowGroups)),
                        dim3(2 * kT), 0, s, a);
     return hipGetLastError();
